@@ -193,3 +193,23 @@ def test_topk_real_valued_ranks():
                     checked += 1
         say(f"  tolerance {rel}: {checked} of {Q * k} ranks resolvable, all agree")
         assert checked >= min_frac * Q * k
+
+
+@pytest.mark.parametrize("k,n", [(1, 1), (7, 3), (50, 1024), (50, 1025), (1024, 1024), (1024, 1025), (300, 4096),
+                                 (300, 4097), (1000, 9000)])
+def test_topk_selection_edges(k, n):
+    """The sizes at which a row's selection changes form (up to 1,024 elements are taken whole, up to 4,096 keys are
+    held on the chip), with ties everywhere: fp32 operands with small integer products, so every score is exact.  The
+    second call merges a chunk into the running list; old and new entries tie too."""
+    from gpu_util import f64, say
+    say(f"[top-k edges] k={k} n={n}")
+    g = W.rng(47, k, n)
+    te = W.integer_array(g, (5, 4), -2, 2, "f32")
+    tr = W.integer_array(g, (n + n // 2 + 1, 4), -2, 2, "f32")
+    te[4] = 0.0   # every score ties
+    want = oracle.scores(te, tr)
+    for rows, chunks in ((n, [(0, n)]), (len(tr), [(0, n), (n, len(tr))]), (len(tr), [(0, len(tr) - n), (len(tr) - n, len(tr))])):
+        wv, wi = oracle.topk(want[:, :rows], k)
+        _, tv, ti = _scores_gpu(te, tr[:rows], topk=k, chunks=chunks, materialize=False)
+        assert np.array_equal(ti, wi)
+        assert np.array_equal(f64(tv), wv)
