@@ -3,7 +3,8 @@
 //
 //   s[q][j] = sum_d te[q][d] * tr[j][d]      (fp32 result)
 //
-// Score GEMM (bf16, fp32 accumulation): one workgroup per 256 x 256 output tile; 4 waves, each
+// Score GEMM (bf16, fp32 accumulation; launches with few or padded tiles take
+// the smaller tiles of k_scores_small): one workgroup per 256 x 256 output tile; 4 waves, each
 // owning a 128 x 128 quadrant as 4 x 4 blocks of 32x32x16 bf16 MFMAs (256
 // fp32 accumulators per lane), 64 contraction columns (one slab) per step.
 // Tiles are ordered so that the workgroups sharing one 256-row train slab are
@@ -293,6 +294,153 @@ __global__ __launch_bounds__(GT, 1) void k_scores_dma(const bf16_bits *__restric
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     store_scores(acc, reinterpret_cast<float *>(smem), s, ld_s, m0, n0, rows_a, rows_b, wm, wn, tid,
                  lane, filt, scale);
+}
+
+// ------------------------------------------------------------------------
+// Small output tiles, for launches whose 256 x 256 tiles are too few for the
+// chip or mostly padding (few queries or few train rows).  A workgroup owns
+// 16 MT queries x 16 NT train rows; its four waves split the contraction into
+// four contiguous bands of 64-column steps, so a 57,344-wide dot product is
+// four chains side by side instead of one.  Each wave copies its own operand
+// rows into a ring of ST stages in LDS (gfx950 buffer_load ... lds, whole
+// 128-byte rows, ST - 1 steps ahead), waits only for its own copies, and
+// multiplies 16x16x32 MFMA fragments read from the ring: no barrier before the
+// final fold, which adds the four partial tiles in fixed order through LDS.
+// The workgroups of one train slab go to one XCD, as in k_scores_dma.
+// Bound by HBM where few queries meet many rows, otherwise by the copies into
+// one CU's LDS (about 80 GB/s a CU; loads of the same fragments into registers
+// reached 50).  Measured, D = 57,344, against the 256 x 256 tiles: 256 x 256
+// rows 954 -> 68 us, 4 queries x 4,096 rows 887 -> 87, 4 x 65,536 1256 -> 1099
+// (6.8 TB/s), 32 x 65,536 1261 -> 1185, 256 x 4,096 956 -> 290.
+//
+// LDS slab: rows of 128 bytes, chunk c of row r at position c ^ ((r >> 1) & 7),
+// so that the 16 rows read by a quarter-wave hit 16 different 16-byte banks.
+template <int MT, int NT, int ST>
+__global__ __launch_bounds__(GT, 1) void k_scores_small(const bf16_bits *__restrict__ te, int64_t ld_te, int Q,
+                                                        const bf16_bits *__restrict__ tr, int64_t ld_tr, int64_t N,
+                                                        int D, float *__restrict__ s, int64_t ld_s, int m_tiles,
+                                                        int n_tiles, ScoreFilter filt, ScoreScale scale) {
+    constexpr int TM = 16 * MT, TN = 16 * NT;
+    constexpr int kRowsBytes = (TM + TN) * 128;        // one stage of one wave
+    constexpr int kCp = (TM + TN) / 8;                 // 1 KB copies per stage
+    static_assert(4 * ST * kRowsBytes <= 160 * 1024, "ring fits in LDS");
+    static_assert((ST - 1) * kCp < 64, "vmcnt range");
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[4 * ST * kRowsBytes];
+
+    const int bid = blockIdx.x;
+    const int xcd = bid % kXcd, local = bid / kXcd;
+    const int mt = local % m_tiles;
+    const int64_t nt = static_cast<int64_t>(local / m_tiles) * kXcd + xcd;
+    if (nt >= n_tiles) return;
+    const int m0 = mt * TM;
+    const int64_t n0 = nt * TN;
+    const int rows_a = Q - m0 < TM ? Q - m0 : TM;
+    const int rows_b = N - n0 < TN ? static_cast<int>(N - n0) : TN;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t ring = lds_addr(smem) + wave * ST * kRowsBytes;
+    uint8_t *ring_p = smem + wave * ST * kRowsBytes;
+
+    const auto rsa = buf_rsrc_uniform(te + static_cast<int64_t>(m0) * ld_te, static_cast<uint32_t>(rows_a * ld_te * 2));
+    const auto rsb = buf_rsrc_uniform(tr + n0 * ld_tr, static_cast<uint32_t>(rows_b * ld_tr * 2));
+    // copy i covers rows 8 i .. 8 i + 7: lane l brings chunk (l & 7) ^ ((row >> 1) & 7) of row 8 i + (l >> 3)
+    int ccol[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) ccol[h] = 8 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7));
+    uint32_t oa[2 * MT], ob[2 * NT];
+#pragma unroll
+    for (int i = 0; i < 2 * MT; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        oa[i] = r < rows_a ? static_cast<uint32_t>((r * ld_te + ccol[i & 1]) * 2) : kBufOOB;
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * NT; ++i) {
+        const int r = 8 * i + (lane >> 3);
+        ob[i] = r < rows_b ? static_cast<uint32_t>((r * ld_tr + ccol[i & 1]) * 2) : kBufOOB;
+    }
+    const int nk = (D + BK - 1) / BK, per = (nk + 3) / 4;
+    const int k_lo = wave * per, k_hi = k_lo + per < nk ? k_lo + per : nk;   // this wave's steps
+    // step t of the band into stage t % ST; columns past D and steps past the
+    // band read as zeros, without a memory access
+    auto issue = [&](int t, int stage) {
+        const int k0 = (k_lo + t) * BK;
+        const bool live = k_lo + t < k_hi;
+        const bool in0 = live && k0 + ccol[0] < D, in1 = live && k0 + ccol[1] < D;
+        const uint32_t dk = static_cast<uint32_t>(k0) * 2u, l0 = ring + stage * kRowsBytes;
+#pragma unroll
+        for (int i = 0; i < 2 * MT; ++i)
+            copy_to_lds(rsa, ((i & 1) ? in1 : in0) ? oa[i] + dk : kBufOOB, l0 + i * 1024);
+#pragma unroll
+        for (int i = 0; i < 2 * NT; ++i)
+            copy_to_lds_nt(rsb, ((i & 1) ? in1 : in0) ? ob[i] + dk : kBufOOB, l0 + (2 * MT + i) * 1024);
+    };
+    const int frow = lane & 15, sw = (frow >> 1) & 7;
+    uint32_t fo[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) fo[h] = static_cast<uint32_t>(frow * 128 + (((lane >> 4) + 4 * h) ^ sw) * 16);
+
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t) issue(t, t);
+    int cur = 0, nxt = ST - 1;
+    for (int t = 0; t < per; ++t) {
+        // step t's copies are done once only those of the ST - 2 later steps remain; this wave's
+        // fragment reads of step t - 1, whose stage the next copies overwrite, are done too
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((ST - 2) * kCp) : "memory");
+        issue(t + ST - 1, nxt);
+        const uint8_t *st = ring_p + cur * kRowsBytes;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 fa[MT], fb[NT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) fa[i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(st + fo[h] + i * 2048));
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                fb[j] = as_bf16x8(*reinterpret_cast<const u32x4 *>(st + fo[h] + (MT + j) * 2048));
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = mfma16_bf16(fa[i], fb[j], acc[i][j]);
+        }
+        cur = cur == ST - 1 ? 0 : cur + 1;
+        nxt = nxt == ST - 1 ? 0 : nxt + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // fold: part[w][m][n] (rows padded by 4 floats), then one output per thread and round
+    constexpr int kPad = TN + 4;
+    static_assert(4 * TM * kPad * 4 <= 4 * ST * kRowsBytes, "the partial tiles fit in the ring");
+    float *part = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                part[(wave * TM + 16 * i + 4 * (lane >> 4) + r) * kPad + 16 * j + (lane & 15)] = acc[i][j][r];
+    __syncthreads();
+    for (int e = tid; e < TM * TN; e += GT) {
+        const int m = e / TN, c = e % TN;
+        if (m >= rows_a || c >= rows_b) continue;
+        const int64_t q = m0 + m, j = n0 + c;
+        float v = (part[m * kPad + c] + part[(TM + m) * kPad + c]) +
+                  (part[(2 * TM + m) * kPad + c] + part[(3 * TM + m) * kPad + c]);
+        if (scale.row) v *= scale.row[q];
+        if (scale.col) v *= scale.col[j];
+        s[q * ld_s + j] = v;
+        if (filt.thr != nullptr && v >= filt.thr[q]) {   // few: the list's counter is taken one at a time
+            const int p = atomicAdd(filt.cnt + q, 1);
+            if (p < filt.cap) {
+                filt.val[q * filt.cap + p] = v;
+                filt.idx[q * filt.cap + p] = static_cast<int>(j);
+            }
+        }
+    }
 }
 
 // fp32 / fp64 operands: every product and sum in float64 (a product of two
@@ -650,20 +798,65 @@ __global__ __launch_bounds__(KT_THREADS) void k_topk_filtered(
 
 }  // namespace
 
+namespace {
+// bf16 score kernels, by output tile: the largest first.  One workgroup fills
+// a CU in each, so a launch takes as many rounds as tiles fall to the busiest
+// XCD's 32 CUs.  A round costs `fixed` plus `per_k` us for every 1,024 columns,
+// measured with all CUs busy (a 256 x 256 tile: 920 us at 57,344 columns and
+// about 30 more for its epilogue; 64 x 64: 265; 16 x 16: 68).  The smallest
+// product of the two is taken: small tiles while they fill an idle chip or
+// spare padding, large ones as soon as their operand reuse counts (256 queries
+// x 4,096 rows: 290 us in 64 x 64 tiles against 956; x 16,384: 1185 against
+// 959).
+struct ScoreTile {
+    int m, n;
+    double fixed, per_k;
+};
+constexpr ScoreTile kScoreTiles[] = {{256, 256, 30., 16.4}, {64, 64, 5., 4.7}, {32, 64, 4., 3.5},
+                                     {16, 64, 4., 2.8},     {32, 32, 3., 2.4}, {16, 16, 3., 1.15}};
+
+int score_tile(int Q, int64_t N, int D) {
+    int best = 0;
+    double cost = 0.;
+    for (int v = 0; v < static_cast<int>(sizeof kScoreTiles / sizeof kScoreTiles[0]); ++v) {
+        const ScoreTile &t = kScoreTiles[v];
+        const int64_t m_tiles = (Q + t.m - 1) / t.m, n_tiles = (N + t.n - 1) / t.n;
+        const int64_t rounds = ((n_tiles + kXcd - 1) / kXcd * m_tiles + 31) / 32;
+        const double c = static_cast<double>(rounds) * (t.fixed + t.per_k * D / 1024.);
+        if (v == 0 || c < cost) {
+            best = v;
+            cost = c;
+        }
+    }
+    return best;
+}
+}  // namespace
+
 hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const void *tr, int tr_dt,
                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s, const ScoreFilter *filt,
                          const ScoreScale &scale, hipStream_t st) {
     if (Q == 0 || N == 0) return hipSuccess;
     if (te_dt == kBF16 && tr_dt == kBF16) {
-        const int m_tiles = (Q + BM - 1) / BM;
-        const int n_tiles = static_cast<int>((N + BN - 1) / BN);
+        const int tile = score_tile(Q, N, D);
+        const int m_tiles = (Q + kScoreTiles[tile].m - 1) / kScoreTiles[tile].m;
+        const int n_tiles = static_cast<int>((N + kScoreTiles[tile].n - 1) / kScoreTiles[tile].n);
         const int n_groups = (n_tiles + kXcd - 1) / kXcd;
         const unsigned grid = static_cast<unsigned>(kXcd) * n_groups * m_tiles;
         const ScoreFilter none{nullptr, nullptr, nullptr, nullptr, 0};
-        hipLaunchKernelGGL(k_scores_dma, dim3(grid), dim3(GT), 0, st, static_cast<const bf16_bits *>(te), ld_te, Q,
-                           static_cast<const bf16_bits *>(tr), ld_tr, N, D, s, ld_s, m_tiles, n_tiles,
-                           filt ? *filt : none, scale);
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(GT), 0, st, static_cast<const bf16_bits *>(te), ld_te, Q,
+                               static_cast<const bf16_bits *>(tr), ld_tr, N, D, s, ld_s, m_tiles, n_tiles,
+                               filt ? *filt : none, scale);
+            return hipGetLastError();
+        };
+        switch (tile) {
+            case 1: return go(k_scores_small<4, 4, 2>);
+            case 2: return go(k_scores_small<2, 4, 3>);
+            case 3: return go(k_scores_small<1, 4, 3>);
+            case 4: return go(k_scores_small<2, 2, 4>);
+            case 5: return go(k_scores_small<1, 1, 8>);
+            default: return go(k_scores_dma);
+        }
     }
     if (filt || te_dt == kBF16 || tr_dt == kBF16) return hipErrorInvalidValue;   // bf16 pairs only with bf16
     const dim3 grid(static_cast<unsigned>((N + FT - 1) / FT), static_cast<unsigned>((Q + FT - 1) / FT));

@@ -213,3 +213,43 @@ def test_topk_selection_edges(k, n):
         _, tv, ti = _scores_gpu(te, tr[:rows], topk=k, chunks=chunks, materialize=False)
         assert np.array_equal(ti, wi)
         assert np.array_equal(f64(tv), wv)
+
+
+@pytest.mark.parametrize("Q,N,D,k,scaled", [
+    (1, 1, 8, 0, False), (17, 15, 72, 3, False), (32, 1100, 648, 5, True),      # 16 x 16 tiles
+    (16, 4097, 200, 0, True), (300, 700, 1024, 9, False),                       # 32 x 32
+    (33, 4100, 1000, 0, False), (5, 20011, 1024, 20, False),                    # 16 x 64
+    (31, 20100, 520, 7, True),                                                  # 32 x 64
+    (65, 16500, 264, 40, True), (256, 4096, 4096, 0, False), (520, 4200, 1096, 11, True),   # 64 x 64
+    (1000, 30000, 72, 30, True), (777, 30100, 200, 0, False)])                  # 256 x 256
+def test_scores_tile_shapes(Q, N, D, k, scaled):
+    """Every output tile of the bf16 GEMM, with remainders in each direction: scores against the oracle's, and the
+    top-k (the long chunks through the candidate filter) exactly that of the scores the same call returned.  fp32
+    sums over D products of unit normals: D 2^-24 sqrt(D) is far below the 1e-5 |g_te| |g_tr| asked."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, f64, host, say
+    say(f"[scores tiles] Q={Q} N={N} D={D} k={k} scaled={scaled}")
+    g = W.rng(48, Q, N, D)
+    te, tr = W.normal(g, (Q, D), 1.0, "bf16"), W.normal(g, (N, D), 1.0, "bf16")
+    row = g.uniform(0.5, 2.0, Q).astype(np.float32) if scaled else None
+    col = g.uniform(0.5, 2.0, N).astype(np.float32) if scaled else None
+    s = torch.full((Q, N + 1), np.nan, dtype=torch.float32, device="cuda")
+    tv = torch.empty((Q, max(k, 1)), dtype=torch.float32, device="cuda")
+    ti = torch.empty((Q, max(k, 1)), dtype=torch.int64, device="cuda")
+    P.logra_influence_scores(dev(te), dev(tr), scores=s[:, :N], topk=k, topk_val=tv if k else None,
+                             topk_idx=ti if k else None, row_scale=dev(row) if scaled else None,
+                             col_scale=dev(col) if scaled else None)
+    got = host(s)
+    assert np.isnan(got[:, N]).all()
+    want = oracle.scores(te, tr)
+    if scaled:
+        want = want * row[:, None] * col[None, :]
+    size = np.linalg.norm(f64(te), axis=1)[:, None] * np.linalg.norm(f64(tr), axis=1)[None, :]
+    if scaled:
+        size = size * row[:, None] * col[None, :]
+    assert np.max(np.abs(f64(got[:, :N]) - want) / size) <= 1e-5
+    if k:
+        wv, wi = oracle.topk(f64(got[:, :N]), k)
+        assert np.array_equal(host(ti), wi)
+        assert np.array_equal(f64(host(tv)), wv)
