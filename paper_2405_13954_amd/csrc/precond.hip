@@ -4,42 +4,55 @@
 //   C = S / N,  lambda = r * tr(C) / D   (r x mean eigenvalue, App. C)
 //   out_q = (C + lambda I)^{-1} g_q
 //
-// All arithmetic is float64; S may be given in fp32 or fp64.  Steps, each batched over layer blocks
-// (blockIdx.y):
-//   1. lambda per block (fixed-order tree sum of the diagonal);
-//   2. A = S/N + lambda I into the workspace (lower triangle);
-//   3. blocked right-looking Cholesky, 64-wide panels: factor the diagonal
-//      block in LDS, solve the panel below it, SYRK-update the trailing
-//      matrix;  a non-positive pivot sets the block's status word;
-//   4. the inverse of each 64x64 diagonal tile of L;
-//   5. blocked forward and backward substitution for 64 right-hand sides per
-//      workgroup, every step a 64x64x64 product on the fp64 matrix cores:
-//        forward   R_i = G_i - sum_{j<i} L_ij Y_j,     Y_i = inv(L_ii) R_i
-//        backward  R_i = Y_i - sum_{j>i} L_ji^T Z_j,   Z_i = inv(L_ii)^T R_i
-//      (tiles staged through LDS with coalesced loads, Y and Z in the
-//      workspace), so no step is a row-by-row recurrence.
+// All arithmetic is float64, the products on the fp64 matrix cores; S may be
+// given in fp32 or fp64.  C + lambda I = L L^T is factored in column panels of
+// 256 (one workgroup per layer block factors a panel's diagonal block and
+// inverts its factor at the same time, W = L_II^{-1}, in registers):
+//
+//   D <= 256    k_factor reads S itself and leaves W; k_solve applies W, then
+//               W^T, to 16 or 32 right-hand sides per workgroup out of LDS.
+//   wider       k_lambda and k_form write A = C + lambda I (lower triangle);
+//               for each panel I: its factor (W_II over A's diagonal block),
+//               k_panel (L_JI = A_JI W_II^T), k_gemm (A_JK -= L_JI L_KI^T for
+//               the columns K of the next panel), k_trail_factor (the other
+//               columns, and the next factor beside them).
+//               Solve, forward: Y_I = W_II R_I (k_solve), R_J -= L_JI Y_I
+//               (k_gemm) for J > I; backward: Z_I = W_II^T Y_I, then
+//               Y_J -= L_IJ^T Z_I for J < I.
+//
+// So no step is a row-by-row recurrence except the 16 x 16 diagonal blocks
+// inside k_factor.
+//
+// Fragments.  A 16x16x4 fp64 MFMA takes from lane l row (column) l % 16 of each
+// operand and contraction index l / 16.  Four of them contract 16 indices
+// ("a unit"); index 2 (l / 16) + kx(i) goes to the i-th, for both operands, so
+// that a row's 16 values are two loads, in each of which four lanes read 64
+// contiguous bytes.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
 namespace logra {
 namespace {
 
-constexpr int NB = 64;   // panel width / tile edge
-constexpr int LT = NB + 1;
+constexpr int PB = 256;   // column panel width
+constexpr int FB = 16;    // block edge inside a panel
+constexpr int kFactorThreads = 512;
+
+__host__ __device__ constexpr int kx(int i) { return 8 * (i >> 1) + (i & 1); }   // 0, 1, 8, 9
 
 struct WsLayout {
-    double *A;      // [n_blocks][D][D], lower triangle: C + lambda I, then L
+    double *A;      // [n_blocks][D][D] panel columns of L below the diagonal blocks, W_II in those
     double *lam;    // [n_blocks]
     int *info;      // [n_blocks] 0 or 1 + first non-positive pivot
-    double *Linv;   // [n_blocks][nbt][64][64] inverses of the diagonal tiles of L
-    double *Y;      // [n_blocks][D][Qp] forward solutions
-    double *Z;      // [n_blocks][D][Qp] backward solutions
+    double *Y;      // [n_blocks][D][Qp] solutions (D > 256)
 };
 
-inline int tiles_of(int D) { return (D + NB - 1) / NB; }
-inline int padded_q(int Q) { return (Q + NB - 1) / NB * NB; }
+inline int padded_q(int Q) { return (Q + 63) / 64 * 64; }
 
 inline WsLayout ws_layout(void *ws, int D, int n_blocks, int Q) {
+    (void)Q;
     char *p = static_cast<char *>(ws);
     const size_t nb = static_cast<size_t>(n_blocks);
     WsLayout w;
@@ -49,12 +62,25 @@ inline WsLayout ws_layout(void *ws, int D, int n_blocks, int Q) {
     p += align256(sizeof(double) * nb);
     w.info = reinterpret_cast<int *>(p);
     p += align256(sizeof(int) * nb);
-    w.Linv = reinterpret_cast<double *>(p);
-    p += align256(sizeof(double) * nb * tiles_of(D) * NB * NB);
     w.Y = reinterpret_cast<double *>(p);
-    p += align256(sizeof(double) * nb * D * padded_q(Q));
-    w.Z = reinterpret_cast<double *>(p);
     return w;
+}
+
+// An element of a gradient array of dtype `dt` (a DtypeCode).
+__device__ __forceinline__ double load_any(const void *p, int dt, int64_t i) {
+    if (dt == kBF16) return load_in_d<bf16_bits>(static_cast<const bf16_bits *>(p) + i);
+    if (dt == kF64) return static_cast<const double *>(p)[i];
+    return load_in_d<float>(static_cast<const float *>(p) + i);
+}
+// f(a value of the element type of dtype `dt`)
+template <typename F>
+__device__ __forceinline__ void with_dtype(int dt, F f) {
+    if (dt == kBF16)
+        f(bf16_bits{});
+    else if (dt == kF64)
+        f(double{});
+    else
+        f(float{});
 }
 
 template <typename TS>
@@ -89,338 +115,669 @@ __global__ __launch_bounds__(256) void k_form(const TS *S, int D, int64_t N, con
     if (i == 0 && threadIdx.x == 0) info[blk] = 0;
 }
 
-// Unblocked Cholesky of the nb x nb diagonal block at (k0, k0); one wave.
-// Lane t holds row t in registers; at step j the pivot and then column j of
-// the rows below come from their lanes by readlane, so no step needs LDS or
-// a barrier.  Each row's update A_tk -= L_tj L_kj is the same fused operation
-// in the same order as a textbook right-looking factorisation.  Entries above
-// the diagonal collect meaningless values and are never read; rows past nb
-// are identity rows, so every step runs (unit pivots there).
-__global__ __launch_bounds__(64) void k_potrf_diag(double *A_all, int D, int k0, int *info) {
-    __shared__ double a[NB * LT];
-    const int blk = blockIdx.x, t = threadIdx.x;
-    double *A = A_all + static_cast<size_t>(blk) * D * D;
-    const int nb = min(NB, D - k0);
-    for (int i = 0; i < nb; ++i)
-        if (t <= i) a[i * LT + t] = A[static_cast<size_t>(k0 + i) * D + k0 + t];
-    __syncthreads();
-    double r[NB];
-    const int tl = t < nb ? t : nb - 1;   // clamped: every lane reads, padding is selected afterwards
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-        const double v = a[tl * LT + (k < tl ? k : tl)];
-        r[k] = t < nb ? (k <= t ? v : 0.0) : (k == t ? 1.0 : 0.0);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        double piv = readlane_d(r[j], j);
-        if (!(piv > 0.0)) {
-            if (t == 0 && info[blk] == 0) info[blk] = k0 + j + 1;
-            piv = 1.0;   // keep going; the result is reported as not PD
-        }
-        const double d = sqrt(piv);
-        r[j] = t == j ? d : t > j ? r[j] / d : r[j];
-#pragma unroll
-        for (int k = j + 1; k < NB; ++k) {
-            r[k] = fma(-r[j], readlane_d(r[j], k), r[k]);
-            if ((k - j) % 8 == 0) __builtin_amdgcn_sched_barrier(0);   // at most 8 readlane pairs live
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-        if (k <= t) a[t * LT + k] = r[k];
-    __syncthreads();
-    for (int i = 0; i < nb; ++i)
-        if (t <= i) A[static_cast<size_t>(k0 + i) * D + k0 + t] = a[i * LT + t];
+// 1 / sqrt(x) to about an ulp: the hardware estimate (relative error below
+// 2^-20) and one third-order step.
+__device__ __forceinline__ double rsqrt_d(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double h = fma(-x * y, y, 1.0);
+    return fma(y * h, fma(h, 0.375, 0.5), y);
 }
 
-// Forward substitution L x = b for one right-hand side per lane, x in
-// registers (b on entry), L the lower-triangular 64 x 64 tile in LDS (row
-// stride LT; past the valid rows an identity), read at wave-uniform
-// addresses so that every read is a broadcast: x_j = x_j / L_jj, then
-// x_k -= L_kj x_j for k > j.
-__device__ __forceinline__ void fwd_subst(double (&x)[NB], const double *l) {
+__device__ __forceinline__ f64x4 mma_unit(const double (&a)[4], const double (&b)[4], f64x4 c) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        x[j] = x[j] / l[j * LT + j];
+    for (int i = 0; i < 4; ++i) c = mfma16_f64(a[i], b[i], c);
+    return c;
+}
+// acc[x][y] += a[x] b[y] over a unit, the four products of one block apart
+template <int FX, int FY>
+__device__ __forceinline__ void mma_units(const double (&a)[FX][4], const double (&b)[FY][4], f64x4 (&acc)[FX][FY]) {
 #pragma unroll
-        for (int k = j + 1; k < NB; ++k) {
-            x[k] = fma(-l[k * LT + j], x[j], x[k]);
-            if ((k - j) % 8 == 0) __builtin_amdgcn_sched_barrier(0);   // at most 8 broadcast reads live
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < FX; ++x)
+#pragma unroll
+            for (int y = 0; y < FY; ++y) acc[x][y] = mfma16_f64(a[x][i], b[y][i], acc[x][y]);
 }
 
-// Rows below the diagonal block: L21 = A21 L11^{-T}; one row per lane.
-__global__ __launch_bounds__(64) void k_trsm_panel(double *A_all, int D, int k0) {
-    __shared__ double l11[NB * LT];
-    __shared__ double x[NB * LT];
-    const int blk = blockIdx.y, t = threadIdx.x;
-    double *A = A_all + static_cast<size_t>(blk) * D * D;
-    const int nb = min(NB, D - k0);
-    const int r0 = k0 + nb + blockIdx.x * NB;
-    const int nr = min(NB, D - r0);
-    for (int i = 0; i < NB; ++i)   // identity past nb
-        l11[i * LT + t] = i < nb ? (t <= i ? A[static_cast<size_t>(k0 + i) * D + k0 + t] : 0.0) : (t == i ? 1.0 : 0.0);
-    for (int i = 0; i < nr; ++i) x[i * LT + t] = (t < nb) ? A[static_cast<size_t>(r0 + i) * D + k0 + t] : 0.0;
-    __syncthreads();
-    // row t solves x L11^T = a, i.e. L11 x^T = a^T
-    double r[NB];
-#pragma unroll
-    for (int k = 0; k < NB; ++k) r[k] = t < nr ? x[t * LT + k] : 0.0;
-    fwd_subst(r, l11);
-#pragma unroll
-    for (int k = 0; k < NB; ++k) x[t * LT + k] = r[k];   // each lane rewrites only its own row
-    __syncthreads();
-    for (int i = 0; i < nr; ++i)
-        if (t < nb) A[static_cast<size_t>(r0 + i) * D + k0 + t] = x[i * LT + t];
-}
+// Barrier for data in LDS alone: memory operations in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Trailing update A22 -= L21 L21^T on lower-triangle 64x64 tiles.
-__global__ __launch_bounds__(256) void k_syrk_update(double *A_all, int D, int k0, int nt) {
-    __shared__ double li[NB * LT];
-    __shared__ double lj[NB * LT];
-    const int blk = blockIdx.y;
-    double *A = A_all + static_cast<size_t>(blk) * D * D;
-    const int nb = min(NB, D - k0);
-    const int base = k0 + nb;
-    // tile t -> (ti >= tj), enumerated row by row of the lower triangle
-    int t = blockIdx.x, ti = 0;
-    while (t > ti) {
-        t -= ti + 1;
-        ++ti;
-    }
-    const int tj = t;
-    const int I = base + ti * NB, J = base + tj * NB;
-    const int tid = threadIdx.x;
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int r = e / NB, c = e - (e / NB) * NB;
-        li[r * LT + c] = (I + r < D && c < nb) ? A[static_cast<size_t>(I + r) * D + k0 + c] : 0.0;
-        lj[r * LT + c] = (J + r < D && c < nb) ? A[static_cast<size_t>(J + r) * D + k0 + c] : 0.0;
-    }
-    __syncthreads();
-    const int ta = tid >> 4, tb = tid & 15;
-    double acc[4][4] = {};
-    for (int m = 0; m < nb; ++m) {
-        double a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            a[u] = li[(4 * ta + u) * LT + m];
-            b[u] = lj[(4 * tb + u) * LT + m];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int i = I + 4 * ta + u;
-        if (i >= D) break;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int j = J + 4 * tb + v;
-            if (j <= i) A[static_cast<size_t>(i) * D + j] -= acc[u][v];
-        }
-    }
-}
-
-// Inverse of the lower-triangular 64x64 diagonal tile t of L (zero padded
-// past D): lane c solves L_tt w = e_c in registers, giving column c.
-__global__ __launch_bounds__(64) void k_diag_inv(const double *A_all, int D, double *Linv_all) {
-    __shared__ double a[NB * LT];
-    const int t = blockIdx.x, blk = blockIdx.y, c = threadIdx.x;
-    const double *A = A_all + static_cast<size_t>(blk) * D * D;
-    const int r0 = t * NB, nb = min(NB, D - r0);
-    for (int i = 0; i < NB; ++i)   // identity past nb
-        a[i * LT + c] = i < nb ? (c <= i ? A[static_cast<size_t>(r0 + i) * D + r0 + c] : 0.0) : (c == i ? 1.0 : 0.0);
-    __syncthreads();
-    double w[NB];   // e_c for the valid columns; padded columns of the inverse are zero
-#pragma unroll
-    for (int k = 0; k < NB; ++k) w[k] = (k == c && c < nb) ? 1.0 : 0.0;
-    fwd_subst(w, a);
-    double *W = Linv_all + (static_cast<size_t>(blk) * gridDim.x + t) * NB * NB;
-#pragma unroll
-    for (int r = 0; r < NB; ++r) W[r * NB + c] = w[r];
-}
-
-// Blocked substitution on the matrix cores for 64 right-hand sides (queries
-// q0 .. q0+63) of one layer block.  Wave w owns rows 16w..16w+15 of the
-// 64 x 64 (rows x queries) tile; acc[c] holds columns 16c..16c+15 in the
-// fp64 16x16 result layout (register r of lane l: row l/16 + 4r).
-// IDENT: the right-hand sides are the identity columns (g is not read) and
-// only the forward solve runs, leaving L^{-1} in Y.
-template <typename TIn, typename TOut, bool IDENT = false>
-__global__ __launch_bounds__(256) void k_trsm_f64(const double *A_all, const double *Linv_all, int D,
-                                                  const TIn *g, int64_t ld_in, int Q, int Qp, double *Y_all,
-                                                  double *Z_all, TOut *out, int64_t ld_out) {
-    __shared__ double La[NB * LT];   // A operand tile [row][k]
-    __shared__ double Yb[NB * LT];   // B operand tile [k][query]
-    const int blk = blockIdx.y, q0 = blockIdx.x * NB;
+// Factor of the (at most) 256 x 256 diagonal block at c0 of each layer block and
+// the inverse W of that factor, whose lower triangle replaces the block's in A.
+// (The factor itself is not needed again.)  One workgroup of 8 waves.
+//
+// Seven waves hold the block as 16 x 16 blocks (hi, lo), lo <= hi, in MFMA
+// accumulators, up to 20 each, transposed and negated.  Step s eliminates block column s
+// of [A; I]: the rows of A below (blocks (i, s)) and the rows of I above
+// (X = L^{-T}, nonzero in blocks (t, s), t <= s) take the same operations.  A
+// block (i, s) of A is final after step s, and X's block (s, i) starts there,
+// so accumulator (hi, lo) holds A(hi, lo) up to step lo and X(lo, hi) from then
+// to step hi.  A step:
+//   1  the owner of (s, s) brings it up to date and hands it over in LDS;
+//   2  the eighth wave factors it, a row per lane, with the rows of I below it
+//      in the next 16 lanes, which end as X_ss = L_ss^{-T}; meanwhile the others
+//      bring their open blocks up to date with step s - 1: acc += P P^T;
+//   3  column s: the owners multiply their blocks by X_ss (a transposed
+//      accumulator is the B operand as it stands) into P, 256 rows of 16 in LDS,
+//      and store those of X, which are rows of W.
+// Rows and columns past the block are identity rows.  With FROM_S (D <= 256)
+// the block is read from S: S / N + lambda I, lambda formed here.
+// Bound by fp64 MFMA issue on one CU (11 MFLOP) and by the chain of the 16
+// pivots of a diagonal block (a SIMD that issues fp64 MFMAs lets one vector
+// instruction of another wave through per MFMA, so the eighth wave's partner
+// has to run dry first).  Measured: 224 blocks of 256 125 us, one 111; with the
+// factor, panel, update and tile-inverse kernels of 64-wide steps before it:
+// 790 us.  All 128 products of panel and pivots in every wave, publication of
+// each column through LDS and both triangles of W stored: 185.
+constexpr int kPRow = FB + 2;   // LDS row in doubles: 144 bytes, the 64 lanes of a fragment read spread evenly
+template <typename TS, bool FROM_S>
+__device__ __forceinline__ void factor_block(const TS *S_all, int64_t N, double r, double *A_all, int D, int c0, int *info,
+                                             int blk) {
+    constexpr int kOwners = 7, kSlots = 20;
+    __shared__ __attribute__((aligned(16))) double P[PB * kPRow];
+    __shared__ __attribute__((aligned(16))) double Dg[FB * kPRow];   // the diagonal block of the step
+    __shared__ __attribute__((aligned(16))) double Xs[FB * kPRow];   // X_ss
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kg = lane >> 4;
-    const int nbt = (D + NB - 1) / NB;
-    const double *L = A_all + static_cast<size_t>(blk) * D * D;
-    const double *Li = Linv_all + static_cast<size_t>(blk) * nbt * NB * NB;
-    double *Y = Y_all + static_cast<size_t>(blk) * D * Qp;
-    double *Z = Z_all + static_cast<size_t>(blk) * D * Qp;
-    f64x4 acc[4];
+    double *A = A_all + static_cast<size_t>(blk) * D * D + static_cast<size_t>(c0) * D + c0;
+    const TS *S = FROM_S ? S_all + static_cast<size_t>(blk) * D * D : nullptr;
+    const int w = D - c0 < PB ? D - c0 : PB, nblk = (w + FB - 1) / FB;
 
-    // Tile staging: each thread's 16 elements are loaded into registers first
-    // (all loads in flight), then stored to LDS.
-    constexpr int kPer = NB * NB / 256;
-    // La[rr][cc] = L[r0+rr][c0+cc] (strictly lower tiles only), or its transpose.
-    auto stage_L = [&](int r0, int c0, bool transpose) {
-        double v[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = tid + 256 * q;
-            const int u = e / NB, w2 = e - (e / NB) * NB;   // consecutive threads: consecutive w2
-            const int rr = transpose ? c0 + u : r0 + u, cc = transpose ? r0 + w2 : c0 + w2;
-            v[q] = (rr < D && cc < D) ? L[static_cast<size_t>(rr) * D + cc] : 0.0;
+    double inv_n = 1.0, lam = 0.0;
+    if (FROM_S) {
+        if (tid < PB) P[tid] = tid < w ? load_in_d<TS>(S + static_cast<size_t>(tid) * D + tid) : 0.0;
+        __syncthreads();
+        for (int o = PB / 2; o > 0; o >>= 1) {
+            if (tid < o) P[tid] += P[tid + o];
+            __syncthreads();
         }
+        lam = r * (P[0] / static_cast<double>(N)) / static_cast<double>(D);
+        inv_n = 1.0 / static_cast<double>(N);
+        __syncthreads();
+    }
+
+    if (wave == kOwners) {   // the eighth wave; its barriers pair with the owners' below
+        int bad = 0;         // 1 + first non-positive pivot
+        for (int s = 0; s < nblk; ++s) {
+            lds_barrier();
+            double x[FB];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = tid + 256 * q;
-            const int u = e / NB, w2 = e - (e / NB) * NB;
-            if (!transpose) La[u * LT + w2] = v[q];
-            else La[w2 * LT + u] = v[q];   // La[w2][u] = L[c0+u][r0+w2]
+            for (int k = 0; k < FB; ++k) x[k] = Dg[row * kPRow + k];
+#pragma unroll
+            for (int k = 0; k < FB; ++k) x[k] = lane < FB ? x[k] : (k == row ? 1.0 : 0.0);
+            // Pivot j's column, then the one update that the next pivot waits for,
+            // then the others beside the next reciprocal root (the order is fixed:
+            // left alone, each column's updates move into the chain of its pivot).
+            double piv = readlane_d(x[0], 0), mine = piv;   // lane j keeps pivot j
+            double inv = rsqrt_d(piv);
+#pragma unroll
+            for (int j = 0; j < FB; ++j) {
+                x[j] *= inv;
+                __builtin_amdgcn_sched_barrier(0);
+                if (j + 1 < FB) {
+                    x[j + 1] = fma(-x[j], readlane_d(x[j], j + 1), x[j + 1]);
+                    piv = readlane_d(x[j + 1], j + 1);
+                    mine = lane == j + 1 ? piv : mine;
+                    __builtin_amdgcn_sched_barrier(0);
+                    inv = rsqrt_d(piv);
+#pragma unroll
+                    for (int k = j + 2; k < FB; ++k) x[k] = fma(-x[j], readlane_d(x[j], k), x[k]);
+                }
+            }
+            // a non-positive pivot spoils what follows it (the call then fails); the first one is kept
+            const uint64_t neg = __builtin_amdgcn_ballot_w64(lane < FB && !(mine > 0.0));
+            if (neg != 0 && bad == 0) bad = c0 + FB * s + 1 + __builtin_ctzll(neg);
+            if (kg == 1) {   // lanes 16-31: rows of X_ss, which are columns of W_ss
+#pragma unroll
+                for (int k = 0; k < FB; ++k) Xs[row * kPRow + k] = x[k];
+#pragma unroll
+                for (int k = 0; k < FB; ++k)
+                    if (k >= row && FB * s + k < w) A[static_cast<size_t>(FB * s + k) * D + FB * s + row] = x[k];
+            }
+            lds_barrier();
+            if (kg == 1) {   // block s of P; the owners are past their reads of the old one
+#pragma unroll
+                for (int k = 0; k < FB; ++k) P[(FB * s + row) * kPRow + k] = x[k];
+            }
+            lds_barrier();
+        }
+        if (lane == 0 && (FROM_S || bad)) {
+            if (FROM_S)
+                info[blk] = bad;
+            else if (info[blk] == 0)
+                info[blk] = bad;
+        }
+        return;
+    }
+
+    // Slot u of a wave is block number wave + 7 u of the lower triangle, row by
+    // row.  Lane u keeps its (hi, lo) (PB: past the last one), so that a step
+    // finds the slots it meets with one ballot.
+    int my_hi = PB, my_lo = PB;
+    {
+        const int b = wave + kOwners * lane;
+        int h = 0;
+        while ((h + 1) * (h + 2) / 2 <= b) ++h;
+        if (lane < kSlots && h < nblk) {
+            my_hi = h;
+            my_lo = b - h * (h + 1) / 2;
+        }
+    }
+    f64x4 acc[kSlots];
+    TS raw[kSlots][4];
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) {
+        const int h = __builtin_amdgcn_readlane(my_hi, u), l = __builtin_amdgcn_readlane(my_lo, u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // -block^T: row kg + 4 q, column `row`
+            const int i = FB * h + row, j = FB * l + kg + 4 * q;
+            const int rr = i > j ? i : j, cc = i > j ? j : i;   // only the lower triangle is read
+            const uint32_t at = rr < w ? static_cast<uint32_t>(rr) * D + cc : 0u;   // past the block: any element
+            raw[u][q] = FROM_S ? S[at] : static_cast<TS>(A[at]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) {
+        const int h = __builtin_amdgcn_readlane(my_hi, u), l = __builtin_amdgcn_readlane(my_lo, u);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = FB * h + row, j = FB * l + kg + 4 * q;
+            double v = static_cast<double>(raw[u][q]);
+            if (FROM_S) v = i == j ? v * inv_n + lam : v * inv_n;
+            acc[u][q] = -((i > j ? i : j) < w ? v : (i == j ? 1.0 : 0.0));
+        }
+    }
+    // LDS byte offsets of the fragments of block rows: uniform part in a register
+    const uint32_t frag0 = static_cast<uint32_t>((row * kPRow + 2 * kg) * 8);
+    constexpr uint32_t kBlkBytes = FB * kPRow * 8;
+    auto load4 = [&](double (&v)[4], int blk_row) {
+        const double *src = reinterpret_cast<const double *>(reinterpret_cast<const char *>(P) + blk_row * kBlkBytes + frag0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = src[kx(i)];
+    };
+    for (int s = 0; s < nblk; ++s) {
+        const int diag = s * (s + 3) / 2 - wave;   // number of block (s, s) less the wave's first
+        const uint32_t own = diag >= 0 && diag % kOwners == 0 ? 1u << (diag / kOwners) : 0u;
+        if (own) {
+#pragma unroll
+            for (int u = 0; u < kSlots; ++u)
+                if (own & (1u << u)) {
+                    if (s > 0) {
+                        double f[4];
+                        load4(f, s);
+                        acc[u] = mma_unit(f, f, acc[u]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) Dg[row * kPRow + kg + 4 * q] = -acc[u][q];
+                }
+        }
+        lds_barrier();
+        if (s > 0) {
+            const uint32_t open = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(my_hi >= s && my_hi < PB)) & ~own;
+            const bool low = my_lo >= s;   // still a block of A
+            const int my_rb = low ? my_hi : my_lo, my_cb = low ? my_lo : my_hi;
+#pragma unroll
+            for (int u = 0; u < kSlots; u += 2) {   // two slots' fragments at a time
+                if (!(open & (3u << u))) continue;
+                double pr[2][4], pc[2][4];
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {   // a slot that is not open reads some block in range
+                    load4(pr[v], __builtin_amdgcn_readlane(my_rb, u + v) & 15);
+                    load4(pc[v], __builtin_amdgcn_readlane(my_cb, u + v) & 15);
+                }
+                if (open & (1u << u)) acc[u] = mma_unit(pc[0], pr[0], acc[u]);
+                if (open & (2u << u)) acc[u + 1] = mma_unit(pc[1], pr[1], acc[u + 1]);
+            }
+        }
+        lds_barrier();
+        const uint32_t col = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64((my_lo == s) != (my_hi == s)));
+        double xs[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xs[q] = -Xs[(kg + 4 * q) * kPRow + row];   // contraction index kg + 4 q
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u)
+            if (col & (1u << u)) {
+                const int h = __builtin_amdgcn_readlane(my_hi, u), l = __builtin_amdgcn_readlane(my_lo, u);
+                const bool low = l == s;
+                const int rb = low ? h : l;
+                double y[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) y[q] = acc[u][q];
+                const f64x4 v = mma_unit(xs, y, f64x4{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+                for (int q = 0; q < 4; ++q) P[(rb * FB + row) * kPRow + kg + 4 * q] = v[q];
+                if (!low) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (FB * s + kg + 4 * q < w)
+                            A[static_cast<size_t>(FB * s + kg + 4 * q) * D + FB * rb + row] = v[q];
+                }
+                acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+            }
+        lds_barrier();
+    }
+}
+
+template <typename TS, bool FROM_S>
+__global__ __launch_bounds__(kFactorThreads, 2) void k_factor(const TS *S_all, int64_t N, double r, double *A_all, int D,
+                                                              int c0, int *info) {
+    factor_block<TS, FROM_S>(S_all, N, r, A_all, D, c0, info, blockIdx.x);
+}
+
+// Y = W R and / or Z = W^T Y for the diagonal block at c0 (width w <= 256, the
+// lower triangle of W in A): one workgroup per 16 NC right-hand sides, which it keeps in LDS ([row][query],
+// padded by 4); 8 waves.  Block rows of 16 are dealt so that waves do equal
+// work on the triangles: wave v takes rows v and 15 - v (NBK = 16 block rows;
+// 8: row v; 4: row v % 4 and half of the columns).  A wave streams its rows (or
+// columns) of W from memory, mostly the L2, four units ahead, and reads the
+// right-hand sides as LDS fragments.  Measured, 224 blocks of 256, 1,024
+// right-hand sides (31 GFLOP): 746 us in workgroups of 32, 885 in workgroups of
+// 64, whose loads and stores no second workgroup of the CU covers; blocked
+// substitution in 64-wide steps took 1,200.
+enum SolveSrc { kFromG = 0, kFromY = 1, kFromIdent = 2 };
+struct SolveArgs {
+    const double *A;       // [n_blocks][D][D]
+    double *Y;             // [n_blocks][D][Qp]
+    const void *g;         // right-hand sides (kFromG)
+    void *out;             // results, or NULL
+    int64_t ld_in, ld_out;
+    int D, c0, Q, Qp, in_dt, out_dt;
+    int src;               // where the right-hand sides come from
+    int fwd, bwd;          // apply W, then W^T
+    int to_y;              // write the result to Y
+};
+
+template <int NBK, int NC>
+__global__ __launch_bounds__(512, 4) void k_solve(SolveArgs p) {
+    constexpr int kLd = 16 * NC + 4;   // fragment reads spread evenly over the banks
+    constexpr int kGroups = NBK == 16 ? 2 : 1;
+    constexpr int kHalves = NBK == 4 && NC > 1 ? 2 : 1;
+    constexpr int kCols = NC / kHalves;
+    constexpr int kBat = NBK == 4 ? 2 : 4;
+    __shared__ __attribute__((aligned(16))) double R[NBK * FB * kLd];
+    const int blk = blockIdx.y, q0 = blockIdx.x * 16 * NC, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kg = lane >> 4;
+    const int D = p.D, w = D - p.c0 < NBK * FB ? D - p.c0 : NBK * FB, nblk = (w + FB - 1) / FB;
+    const double *M = p.A + static_cast<size_t>(blk) * D * D + static_cast<size_t>(p.c0) * D + p.c0;
+    double *Y = p.Y ? p.Y + (static_cast<size_t>(blk) * D + p.c0) * p.Qp : nullptr;
+    const int64_t col0 = static_cast<int64_t>(blk) * D + p.c0;
+
+    // the right-hand sides, eight loads of a thread in flight
+    if (p.src == kFromG) {   // a wave per row of g, consecutive lanes on consecutive elements
+        const int per = (nblk * FB + 63) / 64, all = 2 * NC * per;   // 64-element pieces of the wave's 2 NC rows
+        with_dtype(p.in_dt, [&](auto tag) {
+            using T = decltype(tag);
+            const T *src = static_cast<const T *>(p.g);
+            for (int e0 = 0; e0 < all; e0 += 8) {
+                T v[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int e = e0 + t, q = wave + 8 * (e / per), d = lane + 64 * (e % per);
+                    v[t] = src[e < all && q0 + q < p.Q && d < w ? (q0 + q) * p.ld_in + col0 + d : col0];
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int e = e0 + t, q = wave + 8 * (e / per), d = lane + 64 * (e % per);
+                    if (e < all && d < nblk * FB) R[d * kLd + q] = q0 + q < p.Q && d < w ? load_in_d<T>(&v[t]) : 0.0;
+                }
+            }
+        });
+    } else {
+        const int all = 16 * NC * nblk * FB;
+        for (int e0 = tid; e0 < all; e0 += 8 * 512) {
+            double v[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int e = e0 + 512 * t, d = e / (16 * NC), q = e % (16 * NC);
+                const bool ident = p.src == kFromIdent && q0 + q >= p.c0, in = e < all && d < w && !ident;
+                v[t] = Y[in ? static_cast<size_t>(d) * p.Qp + q0 + q : q0];
+                v[t] = in ? v[t] : ident && p.c0 + d == q0 + q ? 1.0 : 0.0;
+            }
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int e = e0 + 512 * t, d = e / (16 * NC), q = e % (16 * NC);
+                if (e < all) R[d * kLd + q] = v[t];
+            }
+        }
+    }
+    __syncthreads();
+
+    const int ch = kHalves == 2 ? wave >> 2 : 0;   // column half
+    int g[kGroups];
+    g[0] = NBK == 4 ? wave & 3 : wave;
+    if (kGroups == 2) g[kGroups - 1] = 15 - wave;
+    if (NBK == 4 && kHalves == 1 && wave >= 4) g[0] = NBK;   // no rows left
+    // Four values of unit u for row i = 16 gr + row: of W (indices up to i), or of
+    // W^T (indices from i on: a column of W), a wave-uniform base and a lane's
+    // offset.  In the diagonal unit the others are made zero; so are, in the
+    // backward direction, indices past w, which read the workspace behind A
+    // (at most 15 rows; Y alone has 64).  Forward, those lie in diagonal units.
+    const bool ragged = w % FB != 0;
+    auto frag = [&](double (&a)[4], uint32_t off, int u, bool back) {
+        const char *base = reinterpret_cast<const char *>(back ? M + static_cast<size_t>(FB * u) * D : M + FB * u);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            a[t] = *reinterpret_cast<const double *>(base + (back ? static_cast<size_t>(kx(t)) * D : kx(t)) * sizeof(double) + off);
+    };
+    auto mask = [&](double (&a)[4], int gr, int u, bool back) {
+        const int i = FB * gr + row, k0 = FB * u + 2 * kg;
+        const int from = back && u == gr ? i : 0, to = !back && u == gr ? i : w - 1;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = k0 + kx(t) >= from && k0 + kx(t) <= to ? a[t] : 0.0;
+    };
+    f64x4 acc[kGroups][kCols];
+    // Units of a block row go in batches of kBat: one is on its way while the
+    // one before it is multiplied.  (Next to fp64 MFMAs, vector instructions of
+    // the other waves issue one per MFMA, so there are few: addresses are
+    // scalar and only diagonal units are masked.)
+    auto pass = [&](bool back) {
+#pragma unroll
+        for (int x = 0; x < kGroups; ++x) {
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) acc[x][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+            const int gr = g[x];
+            if (gr >= nblk) continue;
+            const int i = FB * gr + row, ic = i < w ? i : 0;
+            const uint32_t off = 8u * (back ? 2u * kg * D + ic : static_cast<uint32_t>(ic) * D + 2u * kg);
+            const int u0 = back ? gr : 0, end = back ? nblk : gr + 1;
+            double a[2][kBat][4];
+#pragma unroll
+            for (int v = 0; v < kBat; ++v)
+                if (u0 + v < end) frag(a[0][v], off, u0 + v, back);
+#pragma unroll
+            for (int t = 0; t < NBK / kBat; ++t) {
+                const int u = u0 + t * kBat;
+                if (u >= end) break;
+#pragma unroll
+                for (int v = 0; v < kBat; ++v)
+                    if (u + kBat + v < end) frag(a[(t + 1) & 1][v], off, u + kBat + v, back);
+#pragma unroll
+                for (int v = 0; v < kBat; ++v) {
+                    if (u + v >= end) break;
+                    double b[kCols][4];
+#pragma unroll
+                    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                        for (int i4 = 0; i4 < 4; ++i4)
+                            b[c][i4] = R[(FB * (u + v) + 2 * kg + kx(i4)) * kLd + 16 * (kCols * ch + c) + row];
+                    if (u + v == gr || (ragged && back && u + v == nblk - 1)) mask(a[t & 1][v], gr, u + v, back);
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+                        for (int c = 0; c < kCols; ++c) acc[x][c] = mfma16_f64(a[t & 1][v][i4], b[c][i4], acc[x][c]);
+                }
+            }
         }
     };
-    auto stage_Linv = [&](int i, bool transpose) {
-        const double *T = Li + static_cast<size_t>(i) * NB * NB;
-        double v[kPer];
+    // f(row, column, value) over the wave's results (of no meaning in rows past w)
+    auto each = [&](auto f) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) v[q] = T[tid + 256 * q];
+        for (int x = 0; x < kGroups; ++x)
+            if (g[x] < nblk) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = tid + 256 * q;
-            const int u = e / NB, w2 = e - (e / NB) * NB;
-            if (!transpose) La[u * LT + w2] = v[q];
-            else La[w2 * LT + u] = v[q];
-        }
+                for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) f(FB * g[x] + kg + 4 * q, 16 * (kCols * ch + c) + row, acc[x][c][q]);
+            }
     };
-    auto stage_B = [&](const double *src, int j) {   // Yb[kk][qq] = src[j*64 + kk][q0 + qq]
-        double v[kPer];
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = tid + 256 * q;
-            const int kk = e / NB, qq = e - (e / NB) * NB;
-            v[q] = (j * NB + kk < D) ? src[static_cast<size_t>(j * NB + kk) * Qp + q0 + qq] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int e = tid + 256 * q;
-            const int kk = e / NB, qq = e - (e / NB) * NB;
-            Yb[kk * LT + qq] = v[q];
-        }
+    auto to_lds = [&]() {
+        __syncthreads();
+        each([&](int d, int q, double v) { R[d * kLd + q] = d < w ? v : 0.0; });
+        __syncthreads();
     };
-    auto mma = [&](double sign) {
+    if (p.fwd) pass(false);
+    if (p.bwd) {
+        if (p.fwd) to_lds();
+        pass(true);
+    }
+    if (p.to_y)
+        each([&](int d, int q, double v) {
+            if (d < w) Y[static_cast<size_t>(d) * p.Qp + q0 + q] = v;
+        });
+    if (p.out) {   // whole rows, through LDS
+        to_lds();
+        with_dtype(p.out_dt, [&](auto tag) {
+            using T = decltype(tag);
+            for (int q = wave; q < 16 * NC && q0 + q < p.Q; q += 8) {
+                T *dst = static_cast<T *>(p.out) + (q0 + q) * p.ld_out + col0;
 #pragma unroll 4
-        for (int s4 = 0; s4 < NB / 4; ++s4) {
-            const double a = sign * La[(16 * w + row) * LT + 4 * s4 + kg];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[c] = mfma16_f64(a, Yb[(4 * s4 + kg) * LT + 16 * c + row], acc[c]);
-        }
-    };
-    auto acc_to_B = [&]() {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Yb[(16 * w + kg + 4 * r) * LT + 16 * c + row] = acc[c][r];
-    };
-    auto zero = [&]() {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
-    };
-    auto store_ws = [&](double *dst, int i) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int d = i * NB + 16 * w + kg + 4 * r;
-                if (d < D) dst[static_cast<size_t>(d) * Qp + q0 + 16 * c + row] = acc[c][r];
+                for (int d = lane; d < w; d += 64) store_out_d<T>(dst + d, R[d * kLd + q]);
             }
-    };
+        });
+    }
+}
 
-    // ---------------- forward: L Y = G ----------------
-    for (int i = 0; i < nbt; ++i) {
+// Panel below the diagonal block at c0: L_J = A_J W^T in place, 32 rows per
+// workgroup.  Wave (rh, ch) has rows 16 rh.., held in registers, and the
+// 16-column blocks c % 2 == ch, which need indices up to their own column only:
+// 72 products of a unit, whose fragments of W arrive eight units ahead.
+__global__ __launch_bounds__(256, 2) void k_panel(double *A_all, int D, int c0) {
+    const int blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rh = wave >> 1, ch = wave & 1, row = lane & 15, kg = lane >> 4;
+    double *A = A_all + static_cast<size_t>(blk) * D * D;
+    const double *M = A + static_cast<size_t>(c0) * D + c0 + static_cast<size_t>(FB * ch) * D;   // the wave's first block
+    const int r0 = c0 + PB + blockIdx.x * 32 + 16 * rh;
+    const int ir = r0 + row < D ? r0 + row : D - 1;
+    const uint32_t oa = 8u * (static_cast<uint32_t>(ir) * D + 2u * kg), ob = 8u * (static_cast<uint32_t>(row) * D + 2u * kg);
+    auto at = [](const double *base, uint32_t off) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + off);
+    };
+    constexpr int kUnits = PB / FB, kAhead = 8;
+    // The units of block 2 c + ch are 0 .. 2 c + 1 (for ch = 0 the last one lies
+    // above the diagonal and is masked whole), so that the list is the same for
+    // both halves: item n is unit n - c (c + 1) of the block with c (c + 1) <= n.
+    constexpr int kItems = kUnits / 2 * (kUnits / 2 + 1);
+    double a[kUnits][4], b[kAhead][4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+    for (int u = 0; u < kUnits; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int q = q0 + 16 * c + row, d = i * NB + 16 * w + kg + 4 * r;
-                if (IDENT)
-                    acc[c][r] = (q < Q && d == q) ? 1.0 : 0.0;
+        for (int t = 0; t < 4; ++t) a[u][t] = at(A + c0 + FB * u + kx(t), oa);
+    auto block_of = [](int n) {
+        return (n >= 2) + (n >= 6) + (n >= 12) + (n >= 20) + (n >= 30) + (n >= 42) + (n >= 56);
+    };
+    auto load = [&](int n) {
+        const int c = block_of(n), u = n - c * (c + 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[n % kAhead][t] = at(M + static_cast<size_t>(2 * FB * c) * D + FB * u + kx(t), ob);
+    };
+#pragma unroll
+    for (int n = 0; n < kAhead; ++n) load(n);
+    __syncthreads();   // both column halves have their rows before either writes
+    f64x4 acc;
+#pragma unroll
+    for (int n = 0; n < kItems; ++n) {
+        const int c = block_of(n), u = n - c * (c + 1);
+        if (u == 0) acc = f64x4{0.0, 0.0, 0.0, 0.0};
+        if (u >= 2 * c) {   // on or past the diagonal: index 16 u + 2 kg + kx(t) up to column 16 (2 c + ch) + row
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                b[n % kAhead][t] = FB * (u - 2 * c - ch) + 2 * kg + kx(t) <= row ? b[n % kAhead][t] : 0.0;
+        }
+        acc = mma_unit(a[u], b[n % kAhead], acc);
+        if (n + kAhead < kItems) load(n + kAhead);
+        if (u == 2 * c + 1) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = r0 + kg + 4 * q;
+                if (i < D) A[static_cast<size_t>(i) * D + c0 + FB * (2 * c + ch) + row] = acc[q];
+            }
+        }
+    }
+}
+
+// C -= A_op B_op over the indices of the panel at c0 (256; fewer in a backward
+// step from the last panel: TAIL).  A wave has FX x FY blocks of 16 x 16, a
+// workgroup WX x WY waves.  Operands come straight from memory (an fp64 MFMA
+// runs 64 cycles, so a wave's loads of a unit, one unit ahead, fit easily),
+// contiguous along the contraction or across it; C is read before the first
+// product and only written at the end.  A 128 x 128 tile takes 54 us where its
+// MFMAs alone take 32; seven 4,096-wide layer blocks' trailing updates 5.1 ms
+// with the factors beside them (13.6 ms in 64-wide steps of scalar fp64 FMAs,
+// 3.9 + 1.8 one after the other).
+constexpr int kTrailGroup = 6;
+enum GemmMode { kTrailNext, kTrailRest, kForward, kBackward };   // A_JK -= L_JI L_KI^T (two parts), the solves
+struct GemmArgs {
+    double *A;
+    double *Y;
+    const void *g;    // first forward step: the right-hand sides are still here
+    int64_t ld_in;
+    int D, c0, Q, Qp, in_dt;
+    int src;          // forward: where C's columns are (kFromIdent: zero from column c0 on)
+};
+
+template <int FX, int FY, int WX, int WY, int MODE, bool TAIL>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &p, int tile, int blk) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kg = lane >> 4;
+    const int D = p.D;
+    double *A = p.A + static_cast<size_t>(blk) * D * D;
+    double *Y = MODE == kTrailNext || MODE == kTrailRest ? nullptr : p.Y + static_cast<size_t>(blk) * D * p.Qp;
+    constexpr bool kTrail = MODE == kTrailNext || MODE == kTrailRest;
+    constexpr int kTx = 16 * FX * WX, kTy = 16 * FY * WY;
+    static_assert(!kTrail || kTx == kTy, "the triangle is cut into squares");
+    int ti, tj;
+    const int base = MODE == kBackward ? 0 : p.c0 + PB;   // first row updated
+    const int rows_end = MODE == kBackward ? p.c0 : D, cols_end = kTrail ? D : p.Qp;
+    constexpr int kW = PB / kTx;   // the next panel's columns are the first kW tile columns
+    if (MODE == kTrailNext) {      // of the lower triangle of tiles, row by row
+        constexpr int kTri = kW * (kW + 1) / 2;
+        ti = tile < kTri ? 0 : kW + (tile - kTri) / kW;
+        if (tile < kTri)
+            while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
+        tj = tile < kTri ? tile - ti * (ti + 1) / 2 : (tile - kTri) % kW;
+    } else if (MODE == kTrailRest) {
+        // The other tile columns: tile rows in groups of kTrailGroup, column by
+        // column within a group, so that the 32 tiles an XCD has in hand at a
+        // time share about 12 operand panels (3 MB, its L2) instead of 33.
+        int g = 0;
+        while (kTrailGroup * kTrailGroup * (g + 1) * (g + 2) / 2 <= tile) ++g;
+        const int rest = tile - kTrailGroup * kTrailGroup * g * (g + 1) / 2;
+        ti = kTrailGroup * g + rest % kTrailGroup;
+        tj = rest / kTrailGroup;
+        if (tj > ti) return;   // a slot above the diagonal
+        ti += kW;
+        tj += kW;
+        if (base + ti * kTx >= D) return;
+    } else {
+        const int nq = p.src == kFromIdent && p.c0 + PB < p.Qp ? p.c0 + PB : p.Qp;
+        const int ntq = (nq + kTy - 1) / kTy;
+        tj = tile % ntq;
+        ti = tile / ntq;
+    }
+    const int i0 = base + ti * kTx + 16 * FX * (wave / WY);
+    const int j0 = (kTrail ? base : 0) + tj * kTy + 16 * FY * (wave % WY);
+    // operands: a wave-uniform base that moves along the contraction, and a
+    // lane's byte offset from it (32 bits where rows of A are meant: A is at most 512 MB)
+    const int64_t sa = MODE == kBackward ? D : 1, sb = kTrail ? 1 : p.Qp;   // step of the contraction index
+    const double *base_a = MODE == kBackward ? A + static_cast<size_t>(p.c0) * D : A + p.c0;
+    const double *base_b = kTrail ? A + p.c0 : Y + static_cast<size_t>(p.c0) * p.Qp;
+    using OffB = std::conditional_t<kTrail, uint32_t, size_t>;   // Y's rows may be long
+    uint32_t oa[FX];
+    OffB ob[FY];
+#pragma unroll
+    for (int x = 0; x < FX; ++x) {
+        const int i = i0 + 16 * x + row, ic = i < rows_end ? i : rows_end - 1;
+        oa[x] = 8u * (MODE == kBackward ? 2u * kg * D + ic : static_cast<uint32_t>(ic) * D + 2u * kg);
+    }
+#pragma unroll
+    for (int y = 0; y < FY; ++y) {
+        const int j = j0 + 16 * y + row, jc = j < cols_end ? j : cols_end - 1;
+        ob[y] = 8u * (kTrail ? static_cast<OffB>(jc) * D + 2u * kg : static_cast<OffB>(2u * kg) * p.Qp + jc);
+    }
+    const int kn = TAIL ? D - p.c0 : PB;   // indices of the panel
+    auto at = [](const double *from, auto off) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(from) + off);
+    };
+    double a[2][FX][4], b[2][FY][4];
+    auto load = [&](int buf, int u) {
+        const double *ba = base_a + FB * u * sa, *bb = base_b + FB * u * sb;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool in = !TAIL || FB * u + 2 * kg + kx(t) < kn;
+#pragma unroll
+            for (int x = 0; x < FX; ++x) a[buf][x][t] = in ? -at(ba + kx(t) * sa, oa[x]) : 0.0;
+#pragma unroll
+            for (int y = 0; y < FY; ++y) b[buf][y][t] = in ? at(bb + kx(t) * sb, ob[y]) : 0.0;
+        }
+    };
+    load(0, 0);
+    f64x4 acc[FX][FY];
+#pragma unroll
+    for (int x = 0; x < FX; ++x)
+#pragma unroll
+        for (int y = 0; y < FY; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
+                const int ic = i < rows_end ? i : rows_end - 1, jc = j < cols_end ? j : cols_end - 1;
+                double v;
+                if (kTrail)
+                    v = A[static_cast<size_t>(ic) * D + jc];
+                else if (MODE == kForward && p.src == kFromG)
+                    v = j < p.Q ? load_any(p.g, p.in_dt, j * p.ld_in + static_cast<int64_t>(blk) * D + ic) : 0.0;
+                else if (MODE == kForward && p.src == kFromIdent && j >= p.c0)
+                    v = 0.0;
                 else
-                    acc[c][r] = (q < Q && d < D) ? load_in_d<TIn>(g + static_cast<int64_t>(q) * ld_in +
-                                                                   static_cast<int64_t>(blk) * D + d)
-                                                 : 0.0;
+                    v = Y[static_cast<size_t>(ic) * p.Qp + jc];
+                acc[x][y][q] = v;
             }
-        for (int j = 0; j < i; ++j) {
-            stage_L(i * NB, j * NB, false);
-            stage_B(Y, j);
-            __syncthreads();
-            mma(-1.0);
-            __syncthreads();
-        }
-        acc_to_B();
-        stage_Linv(i, false);
-        __syncthreads();
-        zero();
-        mma(1.0);
-        store_ws(Y, i);
-        __syncthreads();
+    const int nu = TAIL ? (kn + FB - 1) / FB : PB / FB;
+    for (int u = 0; u < nu; u += 2) {
+        if (u + 1 < nu) load(1, u + 1);
+        mma_units(a[0], b[0], acc);
+        if (u + 2 < nu) load(0, u + 2);
+        if (u + 1 < nu) mma_units(a[1], b[1], acc);
     }
-    if (IDENT) return;
-    // ---------------- backward: L^T Z = Y ----------------
-    for (int i = nbt - 1; i >= 0; --i) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+    for (int x = 0; x < FX; ++x)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int d = i * NB + 16 * w + kg + 4 * r;
-                acc[c][r] = d < D ? Y[static_cast<size_t>(d) * Qp + q0 + 16 * c + row] : 0.0;
+        for (int y = 0; y < FY; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
+                if (i >= rows_end || j >= cols_end) continue;
+                if (kTrail)
+                    A[static_cast<size_t>(i) * D + j] = acc[x][y][q];
+                else
+                    Y[static_cast<size_t>(i) * p.Qp + j] = acc[x][y][q];
             }
-        for (int j = i + 1; j < nbt; ++j) {
-            stage_L(i * NB, j * NB, true);
-            stage_B(Z, j);
-            __syncthreads();
-            mma(-1.0);
-            __syncthreads();
-        }
-        acc_to_B();
-        stage_Linv(i, true);
-        __syncthreads();
-        zero();
-        mma(1.0);
-        store_ws(Z, i);
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int q = q0 + 16 * c + row, d = i * NB + 16 * w + kg + 4 * r;
-                if (q < Q && d < D)
-                    store_out_d<TOut>(out + static_cast<int64_t>(q) * ld_out + static_cast<int64_t>(blk) * D + d,
-                                      acc[c][r]);
-            }
-        __syncthreads();
+}
+
+template <int FX, int FY, int WX, int WY, int MODE, bool TAIL>
+__global__ __launch_bounds__(64 * WX * WY, 2) void k_gemm(GemmArgs p) {
+    gemm_tile<FX, FY, WX, WY, MODE, TAIL>(p, blockIdx.x, blockIdx.y);
+}
+
+// The rest of a trailing update beside the factor of the next panel, which only
+// needs the tiles that are done (kTrailNext): the first n_blocks workgroups
+// factor, so that this chain of pivots, on one CU each, is hidden.  The tiles of
+// all layer blocks follow in one list, of which each XCD (workgroups are dealt
+// to the 8 in turn) takes a contiguous eighth.
+__global__ __launch_bounds__(kFactorThreads, 2) void k_trail_factor(GemmArgs p, int n_blocks, int slots, int *info) {
+    const int b = static_cast<int>(blockIdx.x) - n_blocks;
+    if (b < 0) {
+        factor_block<double, false>(nullptr, 1, 0.0, p.A, p.D, p.c0 + PB, info, blockIdx.x);
+        return;
     }
+    const int per = (n_blocks * slots + 7) / 8, n = (b & 7) * per + (b >> 3);
+    if ((b >> 3) >= per || n >= n_blocks * slots) return;
+    gemm_tile<4, 2, 2, 4, kTrailRest, false>(p, n % slots, n / slots);
 }
 
 __global__ __launch_bounds__(256) void k_clear_info(int *info, int n) {
     for (int i = threadIdx.x; i < n; i += 256) info[i] = 0;
 }
 
-// W = L^{-1} (fp64, rows d, columns q of the forward solution) as two bf16
+// W = L^{-1} (fp64, row d at src + d * ld, zero past the diagonal) as two bf16
 // arrays whose sum carries about 16 significant bits: hi = RNE(W), lo =
 // RNE(W - hi); rows d past D (up to Dp = gridDim.x) are zero.  Split layout:
 // hi [blk][Dp][D] then lo; interleaved: [blk][Dp][2D], the 64 columns of
 // chunk c at 128 c (hi) and 128 c + 64 (lo).  With `ident`, W = I.
-__global__ __launch_bounds__(256) void k_split_w(const double *Y_all, int D, int Qp, bool ident,
+__global__ __launch_bounds__(256) void k_split_w(const double *src_all, int D, int ld, bool ident,
                                                   bool interleaved, bf16_bits *w_hi, bf16_bits *w_lo) {
     const int blk = blockIdx.y, d = blockIdx.x;
     const size_t row = static_cast<size_t>(blk) * gridDim.x + d;
@@ -428,12 +785,12 @@ __global__ __launch_bounds__(256) void k_split_w(const double *Y_all, int D, int
     bf16_bits *l = interleaved ? h + 64 : w_lo + row * D;
     for (int q = threadIdx.x; q < D; q += 256) {
         const int at = interleaved ? q + (q & ~63) : q;   // 128 (q / 64) + q % 64
-        if (d >= D) {
+        if (d >= D || (!ident && q > d)) {
             h[at] = l[at] = 0;
             continue;
         }
         const double y = ident ? (q == d ? 1.0 : 0.0)
-                               : Y_all[static_cast<size_t>(blk) * D * Qp + static_cast<size_t>(d) * Qp + q];
+                               : src_all[static_cast<size_t>(blk) * D * ld + static_cast<size_t>(d) * ld + q];
         const bf16_bits hb = f32_to_bf16_rne(static_cast<float>(y));
         h[at] = hb;
         l[at] = f32_to_bf16_rne(static_cast<float>(y - static_cast<double>(bf16_to_f32(hb))));
@@ -448,14 +805,106 @@ __global__ __launch_bounds__(256) void k_copy_rows(const TIn *src, int64_t ld_in
         store_out_d<TOut>(dst + static_cast<int64_t>(r) * ld_out + c, load_in_d<TIn>(src + static_cast<int64_t>(r) * ld_in + c));
 }
 
-template <typename TIn, typename TOut>
-hipError_t launch_solve(const WsLayout &w, int D, int n_blocks, const void *g, int64_t ld_in, int Q,
-                        void *out, int64_t ld_out, hipStream_t s) {
-    hipLaunchKernelGGL(k_diag_inv, dim3(tiles_of(D), n_blocks), dim3(64), 0, s, w.A, D, w.Linv);
-    const dim3 grid(static_cast<unsigned>(padded_q(Q) / NB), static_cast<unsigned>(n_blocks));
-    hipLaunchKernelGGL((k_trsm_f64<TIn, TOut>), grid, dim3(256), 0, s, w.A, w.Linv, D, static_cast<const TIn *>(g),
-                       ld_in, Q, padded_q(Q), w.Y, w.Z, static_cast<TOut *>(out), ld_out);
+// One k_solve launch over the first `cols` right-hand sides, 32 of them per
+// workgroup (two workgroups share a CU), or 16 where that would leave CUs idle.
+hipError_t launch_solve_block(const SolveArgs &p, int cols, int n_blocks, hipStream_t s) {
+    auto wgs = [&](int nc) { return (cols + 16 * nc - 1) / (16 * nc) * static_cast<int64_t>(n_blocks); };
+    const int nc = wgs(2) >= 256 ? 2 : 1;
+    const dim3 grid(static_cast<unsigned>((cols + 16 * nc - 1) / (16 * nc)), static_cast<unsigned>(n_blocks));
+    const int w = p.D - p.c0 < PB ? p.D - p.c0 : PB;
+    auto go = [&](auto k) {
+        hipLaunchKernelGGL(k, grid, dim3(512), 0, s, p);
+        return hipGetLastError();
+    };
+    if (w <= 64) return nc == 2 ? go(k_solve<4, 2>) : go(k_solve<4, 1>);
+    if (w <= 128) return nc == 2 ? go(k_solve<8, 2>) : go(k_solve<8, 1>);
+    return nc == 2 ? go(k_solve<16, 2>) : go(k_solve<16, 1>);
+}
+
+// One k_gemm launch of a solve, in 64 x 64 tiles.
+template <int MODE>
+hipError_t launch_solve_gemm(const GemmArgs &p, int rows, int cols, int n_blocks, hipStream_t s) {
+    const int64_t tiles = static_cast<int64_t>((rows + 63) / 64) * ((cols + 63) / 64);
+    const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(n_blocks));
+    if (MODE == kBackward && p.D - p.c0 < PB)
+        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, MODE, MODE == kBackward>), grid, dim3(256), 0, s, p);
+    else
+        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, MODE, false>), grid, dim3(256), 0, s, p);
     return hipGetLastError();
+}
+
+// The trailing update of the panel at c0 and the factor of the next one: first
+// the next panel's columns, in 64 x 64 tiles while 128 x 128 ones would leave
+// CUs idle, then the rest (128 x 128 tiles) beside the factor.
+hipError_t launch_trail(const GemmArgs &p, int rest, int n_blocks, int *info, hipStream_t s) {
+    auto next = [&](int t) {   // tiles of the next panel's columns
+        const int r = (rest + t - 1) / t, w = PB / t;
+        return r < w ? r * (r + 1) / 2 : w * (w + 1) / 2 + (r - w) * w;
+    };
+    if (next(128) * n_blocks >= 256)
+        hipLaunchKernelGGL((k_gemm<4, 2, 2, 4, kTrailNext, false>), dim3(next(128), n_blocks), dim3(512), 0, s, p);
+    else
+        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, kTrailNext, false>), dim3(next(64), n_blocks), dim3(256), 0, s, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int r = (rest + 127) / 128 - PB / 128, groups = r > 0 ? (r + kTrailGroup - 1) / kTrailGroup : 0;
+    const int slots = kTrailGroup * kTrailGroup * groups * (groups + 1) / 2;
+    hipLaunchKernelGGL(k_trail_factor, dim3(n_blocks + (n_blocks * slots + 7) / 8 * 8), dim3(kFactorThreads), 0, s, p, n_blocks,
+                       slots, info);
+    return hipGetLastError();
+}
+
+// W (D <= 256), or the panels of L and every W_II: the factorisation.
+hipError_t launch_factor(const void *S, bool s_f64, int D, int n_blocks, int64_t N, double damp_ratio,
+                         const WsLayout &w, hipStream_t s) {
+    const double *Sd = static_cast<const double *>(S);
+    const float *Sf = static_cast<const float *>(S);
+    if (D <= PB) {
+        if (s_f64)
+            hipLaunchKernelGGL((k_factor<double, true>), dim3(n_blocks), dim3(kFactorThreads), 0, s, Sd, N, damp_ratio,
+                               w.A, D, 0, w.info);
+        else
+            hipLaunchKernelGGL((k_factor<float, true>), dim3(n_blocks), dim3(kFactorThreads), 0, s, Sf, N, damp_ratio,
+                               w.A, D, 0, w.info);
+        return hipGetLastError();
+    }
+    if (s_f64) {
+        hipLaunchKernelGGL(k_lambda<double>, dim3(n_blocks), dim3(256), 0, s, Sd, D, N, damp_ratio, w.lam);
+        hipLaunchKernelGGL(k_form<double>, dim3(D, n_blocks), dim3(256), 0, s, Sd, D, N, w.lam, w.A, w.info);
+    } else {
+        hipLaunchKernelGGL(k_lambda<float>, dim3(n_blocks), dim3(256), 0, s, Sf, D, N, damp_ratio, w.lam);
+        hipLaunchKernelGGL(k_form<float>, dim3(D, n_blocks), dim3(256), 0, s, Sf, D, N, w.lam, w.A, w.info);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_factor<double, false>), dim3(n_blocks), dim3(kFactorThreads), 0, s,
+                       static_cast<const double *>(nullptr), N, damp_ratio, w.A, D, 0, w.info);
+    e = hipGetLastError();
+    for (int c0 = 0; c0 + PB < D && e == hipSuccess; c0 += PB) {
+        const int rest = D - c0 - PB;
+        hipLaunchKernelGGL(k_panel, dim3((rest + 31) / 32, n_blocks), dim3(256), 0, s, w.A, D, c0);
+        if ((e = hipGetLastError()) != hipSuccess) break;
+        e = launch_trail(GemmArgs{w.A, nullptr, nullptr, 0, D, c0, 0, 0, kF32, kFromY}, rest, n_blocks, w.info, s);
+    }
+    return e;
+}
+
+// Forward solve, D > 256: Y = L^{-1} g (src kFromG) or L^{-1} (kFromIdent, Q = D:
+// only the columns up to each block are formed).
+hipError_t launch_forward(const WsLayout &w, int D, int n_blocks, const void *g, int in_dt, int64_t ld_in, int Q, int src,
+                          hipStream_t s) {
+    const int Qp = padded_q(Q);
+    hipError_t e = hipSuccess;
+    for (int c0 = 0; c0 < D && e == hipSuccess; c0 += PB) {
+        const int from = src == kFromG && c0 > 0 ? static_cast<int>(kFromY) : src;
+        const int cols = src == kFromIdent && c0 + PB < Qp ? c0 + PB : Qp;
+        e = launch_solve_block(SolveArgs{w.A, w.Y, g, nullptr, ld_in, 0, D, c0, Q, Qp, in_dt, kF32, from, 1, 0, 1}, cols,
+                               n_blocks, s);
+        const int rest = D - c0 - PB;
+        if (rest <= 0 || e != hipSuccess) continue;
+        e = launch_solve_gemm<kForward>(GemmArgs{w.A, w.Y, g, ld_in, D, c0, Q, Qp, in_dt, from}, rest, cols, n_blocks, s);
+    }
+    return e;
 }
 
 }  // namespace
@@ -478,8 +927,7 @@ bf16_bits *self_influence_w(void *ws, int D, int n_blocks, bool lo) {
 size_t precond_ws_bytes(int D, int n_blocks, int Q) {
     const size_t nb = static_cast<size_t>(n_blocks);
     return align256(sizeof(double) * nb * D * D) + align256(sizeof(double) * nb) + align256(sizeof(int) * nb) +
-           align256(sizeof(double) * nb * tiles_of(D) * NB * NB) +
-           2 * align256(sizeof(double) * nb * D * padded_q(Q));
+           align256(sizeof(double) * nb * D * padded_q(Q));
 }
 
 int *precond_info_ptr(void *ws, int D, int n_blocks) { return ws_layout(ws, D, n_blocks, 0).info; }
@@ -517,32 +965,21 @@ hipError_t launch_precondition(const void *S, bool s_f64, int D, int n_blocks, i
                                const void *g_test, int in_dt, int64_t ld_in, int Q, void *g_out, int out_dt,
                                int64_t ld_out, void *ws, hipStream_t s) {
     const WsLayout w = ws_layout(ws, D, n_blocks, Q);
-    if (s_f64) {
-        const double *Sd = static_cast<const double *>(S);
-        hipLaunchKernelGGL(k_lambda<double>, dim3(n_blocks), dim3(256), 0, s, Sd, D, N, damp_ratio, w.lam);
-        hipLaunchKernelGGL(k_form<double>, dim3(D, n_blocks), dim3(256), 0, s, Sd, D, N, w.lam, w.A, w.info);
-    } else {
-        const float *Sf = static_cast<const float *>(S);
-        hipLaunchKernelGGL(k_lambda<float>, dim3(n_blocks), dim3(256), 0, s, Sf, D, N, damp_ratio, w.lam);
-        hipLaunchKernelGGL(k_form<float>, dim3(D, n_blocks), dim3(256), 0, s, Sf, D, N, w.lam, w.A, w.info);
+    hipError_t e = launch_factor(S, s_f64, D, n_blocks, N, damp_ratio, w, s);
+    if (e != hipSuccess || Q == 0) return e;
+    const int Qp = padded_q(Q);
+    if (D <= PB)
+        return launch_solve_block(SolveArgs{w.A, nullptr, g_test, g_out, ld_in, ld_out, D, 0, Q, Qp, in_dt, out_dt, kFromG,
+                                            1, 1, 0},
+                                  Q, n_blocks, s);
+    e = launch_forward(w, D, n_blocks, g_test, in_dt, ld_in, Q, kFromG, s);
+    for (int c0 = (D - 1) / PB * PB; c0 >= 0 && e == hipSuccess; c0 -= PB) {
+        e = launch_solve_block(SolveArgs{w.A, w.Y, nullptr, g_out, 0, ld_out, D, c0, Q, Qp, kF32, out_dt, kFromY, 0, 1, 1},
+                               Qp, n_blocks, s);
+        if (c0 == 0 || e != hipSuccess) continue;
+        e = launch_solve_gemm<kBackward>(GemmArgs{w.A, w.Y, nullptr, 0, D, c0, Q, Qp, kF32, kFromY}, c0, Qp, n_blocks, s);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (int k0 = 0; k0 < D; k0 += NB) {
-        hipLaunchKernelGGL(k_potrf_diag, dim3(n_blocks), dim3(64), 0, s, w.A, D, k0, w.info);
-        const int rest = D - k0 - NB;
-        if (rest > 0) {
-            const int nt = (rest + NB - 1) / NB;
-            hipLaunchKernelGGL(k_trsm_panel, dim3(nt, n_blocks), dim3(64), 0, s, w.A, D, k0);
-            hipLaunchKernelGGL(k_syrk_update, dim3(nt * (nt + 1) / 2, n_blocks), dim3(256), 0, s, w.A, D, k0, nt);
-        }
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (Q == 0) return hipSuccess;
-    return with_types(in_dt, out_dt, [&](auto ti, auto to) {
-        return launch_solve<decltype(ti), decltype(to)>(w, D, n_blocks, g_test, ld_in, Q, g_out, ld_out, s);
-    });
+    return e;
 }
 
 hipError_t launch_inverse_factor(const float *S, int D, int n_blocks, int64_t N, double damp_ratio,
@@ -550,21 +987,21 @@ hipError_t launch_inverse_factor(const float *S, int D, int n_blocks, int64_t N,
     const WsLayout w = ws_layout(ws, D, n_blocks, D);
     bf16_bits *hi = self_influence_w(ws, D, n_blocks, false), *lo = self_influence_w(ws, D, n_blocks, true);
     const bool ident = damp_ratio < 0;
+    const double *src = w.A;   // D <= 256: W itself
+    int ld = D;
     if (!ident) {
-        // factor (status words as for the preconditioner), then L^{-1} = forward solve of I
-        const hipError_t e = launch_precondition(S, false, D, n_blocks, N, damp_ratio, nullptr, kF32, D, 0,
-                                                 nullptr, kF32, D, ws, s);
+        hipError_t e = launch_factor(S, false, D, n_blocks, N, damp_ratio, w, s);
+        if (e == hipSuccess && D > PB) {   // L^{-1}: forward solve of the identity
+            e = launch_forward(w, D, n_blocks, nullptr, kF32, 0, D, kFromIdent, s);
+            src = w.Y;
+            ld = padded_q(D);
+        }
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_diag_inv, dim3(tiles_of(D), n_blocks), dim3(64), 0, s, w.A, D, w.Linv);
-        const dim3 grid(static_cast<unsigned>(padded_q(D) / NB), static_cast<unsigned>(n_blocks));
-        hipLaunchKernelGGL((k_trsm_f64<float, float, true>), grid, dim3(256), 0, s, w.A, w.Linv, D,
-                           static_cast<const float *>(nullptr), int64_t{0}, D, padded_q(D), w.Y, w.Z,
-                           static_cast<float *>(nullptr), int64_t{0});
     } else {
         hipLaunchKernelGGL(k_clear_info, dim3(1), dim3(256), 0, s, w.info, n_blocks);
     }
-    hipLaunchKernelGGL(k_split_w, dim3((D + 255) / 256 * 256, n_blocks), dim3(256), 0, s, w.Y, D, padded_q(D),
-                       ident, interleaved, hi, lo);
+    hipLaunchKernelGGL(k_split_w, dim3((D + 255) / 256 * 256, n_blocks), dim3(256), 0, s, src, D, ld, ident, interleaved, hi,
+                       lo);
     return hipGetLastError();
 }
 

@@ -218,3 +218,57 @@ def test_precondition_not_pd():
         P.logra_precondition(dev(S2), 1, 0.0, dev(v), out)
     assert ei.value.status == P.ERR_NOT_PD
     assert "pivot 10" in P.logra_last_error()
+
+
+@pytest.mark.parametrize("D,nb,Q,idt,odt", [
+    (8, 3, 1, "f32", "f64"), (16, 2, 17, "f64", "f64"), (17, 1, 65, "f32", "f32"), (63, 2, 16, "bf16", "f64"),
+    (65, 2, 33, "f32", "f64"), (129, 3, 5, "f32", "f64"), (255, 2, 64, "f64", "bf16"), (256, 300, 3, "bf16", "f64"),
+    (256, 5, 1000, "f32", "f64"), (257, 2, 5, "f32", "f64"), (300, 1, 70, "bf16", "f32"), (512, 2, 129, "f64", "f64"),
+    (777, 2, 9, "f32", "f64"), (1024, 4, 64, "f32", "f64"), (1288, 1, 200, "bf16", "f64")])
+def test_precondition_panel_edges(D, nb, Q, idt, odt):
+    """Widths around the 16-wide blocks, the 256-wide panels and their remainders, numbers of right-hand sides around
+    the 16, 32 and 64 of a workgroup, and both solve paths.  A float64 solve of a system of condition number kappa is
+    within about D kappa 2^-53 of the oracle's; kappa <= 1 + 10 D here (damping 0.1 of the mean eigenvalue), so 1e-10
+    leaves a factor of 50 at the widest; outputs in fewer bits add their rounding."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, host, rowwise_normwise, say
+    say(f"[precondition panels] D={D} blocks={nb} Q={Q} in={idt} out={odt}")
+    N = 50
+    few = min(nb, 3)
+    S = np.stack([W.spd_matrix(60 + l, D, min(D, 40), scale=float(N)) for l in range(few)])
+    up = np.triu(np.ones((D, D), bool), 1)
+    Sd = S.copy()
+    Sd[:, up] = np.nan                       # never read
+    Sd = Sd[np.arange(nb) % few]
+    g = W.normal(W.rng(61, D), (Q, nb * D), 1.0, "bf16" if idt == "bf16" else "f32")
+    g = g.astype(np.float64) / 3.0 if idt == "f64" else g
+    out = torch.full((Q, nb * D + 3), float("nan"),
+                     dtype={"f32": torch.float32, "f64": torch.float64, "bf16": torch.bfloat16}[odt], device="cuda")
+    P.logra_precondition_blocks(dev(Sd), N, 0.1, dev(g), out[:, :nb * D])
+    got = host(out)
+    tail = got[:, nb * D:]
+    assert np.isnan(W.bf16_bits_to_f32(tail) if odt == "bf16" else tail).all()
+    tol = {"f64": 1e-10, "f32": 1e-6, "bf16": 5e-3}[odt]
+    for l in sorted({0, 1 % nb, nb // 2, nb - 1}):
+        want, _ = oracle.precondition(S[l % few].astype(np.float64), N, 0.1, np.ascontiguousarray(g[:, l * D:(l + 1) * D]))
+        err = rowwise_normwise(got[:, l * D:(l + 1) * D], want)
+        say(f"  block {l}: normwise err {err:.3e} (tol {tol})")
+        assert err <= tol
+
+
+@pytest.mark.parametrize("D,at", [(64, 0), (200, 199), (256, 100), (300, 280), (600, 511), (600, 512)])
+def test_precondition_not_pd_pivot(D, at):
+    """The first non-positive pivot is named, in whichever block or panel it falls."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, say
+    say(f"[precondition not PD] D={D} pivot {at}")
+    S = np.stack([np.eye(D, dtype=np.float32)] * 3)
+    S[1, at, at] = -1.0
+    S[2, at, at] = -1.0
+    out = torch.zeros((2, 3 * D), dtype=torch.float32, device="cuda")
+    with pytest.raises(P.LograError) as ei:
+        P.logra_precondition_blocks(dev(S), 1, 0.0, dev(np.ones((2, 3 * D), np.float32)), out)
+    assert ei.value.status == P.ERR_NOT_PD
+    assert f"block 1: pivot {at} " in P.logra_last_error()
