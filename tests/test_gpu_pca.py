@@ -265,3 +265,28 @@ def test_pca_from_masked_activations_end_to_end():
         assert sin <= 1e-3, (r, sin)
         assert s > 0 or np.sort(np.abs(want[r]))[-1] - np.sort(np.abs(want[r]))[-2] < 1e-3
     assert np.max(np.abs(ev - wev) / wev) <= 1e-4
+
+
+@pytest.mark.parametrize("ns", [[5800, 264, 2056], [2056, 2048, 1032, 776, 768, 520], [5640]])
+def test_act_cov_tile_orders(ns):
+    """The three orders in which a launch's tiles go to the XCDs: chunks of 32 of a list of several factors (more than
+    256 tiles), eighths of a shorter one, and whole groups of one long factor.  Small integers, so every entry is
+    exact; the list of a group and the groups of a single call must give the same C."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    say(f"[act cov tile orders] n={ns}")
+    B, T = 2, 33
+    gen = W.torch_generator(64, len(ns))
+    mask = torch.ones((B, T), dtype=torch.uint8, device="cuda")
+    mask[1, 9:] = 0
+    acts = [torch.randint(-3, 4, (B, T, n), generator=gen, device="cuda").bfloat16() for n in ns]
+    Cs = [torch.zeros((n, n), device="cuda") for n in ns]
+    P.logra_act_cov_accumulate_group(list(zip(acts, Cs)), mask=mask)
+    for a, C in zip(acts, Cs):
+        v = a[mask.bool()].float()
+        want = torch.mm(v.t().contiguous(), v)
+        assert torch.equal(C, want)
+        single = torch.zeros_like(C)
+        P.logra_act_cov_accumulate(a, single, mask=mask)
+        assert torch.equal(single, want)
