@@ -776,24 +776,26 @@ __global__ __launch_bounds__(256) void k_clear_info(int *info, int n) {
 // arrays whose sum carries about 16 significant bits: hi = RNE(W), lo =
 // RNE(W - hi); rows d past D (up to Dp = gridDim.x) are zero.  Split layout:
 // hi [blk][Dp][D] then lo; interleaved: [blk][Dp][2D], the 64 columns of
-// chunk c at 128 c (hi) and 128 c + 64 (lo).  With `ident`, W = I.
+// chunk c at 128 c (hi) and behind them (lo).  With `ident`, W = I.
 __global__ __launch_bounds__(256) void k_split_w(const double *src_all, int D, int ld, bool ident,
                                                   bool interleaved, bf16_bits *w_hi, bf16_bits *w_lo) {
     const int blk = blockIdx.y, d = blockIdx.x;
     const size_t row = static_cast<size_t>(blk) * gridDim.x + d;
     bf16_bits *h = interleaved ? w_hi + row * 2 * D : w_hi + row * D;
-    bf16_bits *l = interleaved ? h + 64 : w_lo + row * D;
+    bf16_bits *l = interleaved ? h : w_lo + row * D;
     for (int q = threadIdx.x; q < D; q += 256) {
-        const int at = interleaved ? q + (q & ~63) : q;   // 128 (q / 64) + q % 64
+        const int c0 = q & ~63;
+        const int at = interleaved ? q + c0 : q;   // 128 (q / 64) + q % 64
+        const int at_lo = interleaved ? at + min(64, D - c0) : q;
         if (d >= D || (!ident && q > d)) {
-            h[at] = l[at] = 0;
+            h[at] = l[at_lo] = 0;
             continue;
         }
         const double y = ident ? (q == d ? 1.0 : 0.0)
                                : src_all[static_cast<size_t>(blk) * D * ld + static_cast<size_t>(d) * ld + q];
         const bf16_bits hb = f32_to_bf16_rne(static_cast<float>(y));
         h[at] = hb;
-        l[at] = f32_to_bf16_rne(static_cast<float>(y - static_cast<double>(bf16_to_f32(hb))));
+        l[at_lo] = f32_to_bf16_rne(static_cast<float>(y - static_cast<double>(bf16_to_f32(hb))));
     }
 }
 
@@ -922,6 +924,11 @@ bf16_bits *self_influence_w(void *ws, int D, int n_blocks, bool lo) {
     char *p = static_cast<char *>(ws) + precond_ws_bytes(D, n_blocks, D);
     if (lo) p += w_half_bytes(D, n_blocks);
     return reinterpret_cast<bf16_bits *>(p);
+}
+
+float *self_influence_part(void *ws, int D, int n_blocks, size_t *bytes) {
+    *bytes = sizeof(double) * static_cast<size_t>(n_blocks) * D * padded_q(D);
+    return reinterpret_cast<float *>(ws_layout(ws, D, n_blocks, D).Y);
 }
 
 size_t precond_ws_bytes(int D, int n_blocks, int Q) {

@@ -10,18 +10,13 @@
 // 16 significant bits together), so the products run on the bf16 matrix
 // cores with fp32 accumulation: y = g W_hi^T + g W_lo^T.
 //
-// bf16 gradients with D a multiple of 32: one workgroup per 256 gradients;
-// for each block and each
-// 256-wide pass over the output dimension, the contraction advances 32
-// columns (one slab) per step: the slab of the gradients and of both W halves
-// is fetched one step ahead into registers (range-checked buffer loads; rows
-// and columns past the data read as zeros) and stored into one of two LDS
-// buffers (80-byte rows, conflict-free fragment reads); 4 waves, each owning
-// 128 gradients x 128 outputs as 4 x 4 blocks of 32x32x16 MFMAs.  After the
-// last slab of a pass the squares of the outputs are summed over the wave's
-// columns (registers, then DPP lane permutations inside rows of 16 lanes)
-// into the gradients' running sums; at the end the partial sums are added
-// through LDS, in a fixed order.
+// bf16 gradients: one workgroup per 256 gradients and range of blocks, 256 output
+// dimensions per pass as 4 waves x (4 x 4 32x32x16 MFMA blocks), operands
+// copied straight into an LDS ring; W is lower triangular and the MFMAs above
+// its diagonal are left out.  After the last slab of a pass the squares of the
+// outputs are summed over the wave's columns (registers, then DPP lane
+// permutations inside rows of 16 lanes) into the gradients' running sums; at
+// the end the partial sums are added through LDS, in a fixed order.
 #include <type_traits>
 
 #include "common.h"
@@ -33,10 +28,7 @@ namespace {
 
 constexpr int SR = 256;                    // gradients per workgroup
 constexpr int SO = 256;                    // output dimensions per pass
-constexpr int SK = 32;                     // contraction columns per slab
-constexpr int SLD = SK + 8;                // padded LDS row (bf16): 80 bytes
 constexpr int STH = 256;                   // threads
-constexpr int SL = SR * SK / 8 / STH;      // 128-bit loads per operand and thread per slab (4)
 
 // DPP lane permutations within rows of 16 lanes (dpp_ctrl encodings)
 constexpr int kDppXor1 = 0xB1;             // quad_perm [1, 0, 3, 2]
@@ -114,146 +106,33 @@ __device__ __forceinline__ void finish_rows(const float (&psum)[4], float *rowsu
     }
 }
 
-struct Slab3 {
-    u32x4 a[SL], h[SL], l[SL];
-};
-
-__global__ __launch_bounds__(STH, 1) void k_self_influence(const bf16_bits *__restrict__ g, int64_t ld,
-                                                           int64_t rows, int D, int n_blocks,
-                                                           const bf16_bits *__restrict__ w_hi,
-                                                           const bf16_bits *__restrict__ w_lo,
-                                                           float *__restrict__ self_out,
-                                                           float *__restrict__ rsqrt_out) {
-    __shared__ __attribute__((aligned(16))) bf16_bits As[2][SR * SLD];
-    __shared__ __attribute__((aligned(16))) bf16_bits Hs[2][SO * SLD];
-    __shared__ __attribute__((aligned(16))) bf16_bits Ls[2][SO * SLD];
-    __shared__ float rowsum[2][2][SR];
-
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * SR;
-    const int nrows = rows - r0 < SR ? static_cast<int>(rows - r0) : SR;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int n_ot = (D + SO - 1) / SO;
-    const int Dp = n_ot * SO;        // rows of each W half, zero past D
-    const int ns = (D + SK - 1) / SK;
-    const int ns2 = ns + (ns & 1);   // slabs per output pass, rounded up to even (extra slabs load zeros)
-
-    // staging: load i of a thread covers row (or output) srow + 64 i, columns scol..scol+7
-    const int srow = tid >> 2, scol = 8 * (tid & 3);
-    const auto rsa = buf_rsrc_uniform(g + r0 * ld, static_cast<uint32_t>(nrows * ld * 2));
-    uint32_t oa[SL];
-#pragma unroll
-    for (int i = 0; i < SL; ++i) {
-        const int r = srow + 64 * i;
-        oa[i] = r < nrows ? static_cast<uint32_t>((r * ld + scol) * 2) : kBufOOB;
-    }
-    // load cursor: slab (ls, lot, ll) = (contraction slab, output pass, block),
-    // advanced by one slab per gload in the order the slabs are consumed
-    int ls = 0, lot = 0, ll = 0;
-    auto gload = [&](Slab3 &st) {
-        const bool live = ll < n_blocks && ls < ns;   // uniform (D is a multiple of SK)
-        const int col = ls * SK + scol;
-        const bool cin = live;
-        const uint32_t da = static_cast<uint32_t>((static_cast<int64_t>(ll) * D + ls * SK) * 2);
-        const size_t wblk = static_cast<size_t>(live ? ll : 0) * Dp * D;
-        const auto rh = buf_rsrc_uniform(w_hi + wblk, static_cast<uint32_t>(Dp * D * 2));
-        const auto rl = buf_rsrc_uniform(w_lo + wblk, static_cast<uint32_t>(Dp * D * 2));
-#pragma unroll
-        for (int i = 0; i < SL; ++i) {
-            const int o = lot * SO + srow + 64 * i;   // output dimension = row of W (zero rows past D)
-            const uint32_t ow = cin ? static_cast<uint32_t>((o * D + col) * 2) : kBufOOB;
-            st.a[i] = buf_ld128(rsa, cin ? oa[i] + da : kBufOOB);
-            st.h[i] = buf_ld128(rh, ow);
-            st.l[i] = buf_ld128(rl, ow);
-        }
-        if (++ls == ns2) {
-            ls = 0;
-            if (++lot == n_ot) {
-                lot = 0;
-                ++ll;
-            }
-        }
-    };
-    auto lstore = [&](const Slab3 &st, int buf) {
-#pragma unroll
-        for (int i = 0; i < SL; ++i) {
-            const int off = (srow + 64 * i) * SLD + scol;
-            *reinterpret_cast<u32x4 *>(&As[buf][off]) = st.a[i];
-            *reinterpret_cast<u32x4 *>(&Hs[buf][off]) = st.h[i];
-            *reinterpret_cast<u32x4 *>(&Ls[buf][off]) = st.l[i];
-        }
-    };
-
-    Acc acc;
-    float psum[4] = {0.f, 0.f, 0.f, 0.f};   // row sums (fold_rows)
-    zero_acc(acc);
-
-    // fragments: lane l reads row (l % 32) of each 32-row block, columns
-    // 8 (l / 32) .. +8 of each 16-wide step
-    const int frow = lane & 31, fk = 8 * (lane >> 5);
-    auto compute = [&](int buf) {
-#pragma unroll
-        for (int ks = 0; ks < SK / 16; ++ks) {
-            bf16x8 fa[4], fh[4], fl[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                fa[i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                    &As[buf][(wm * 128 + i * 32 + frow) * SLD + fk + 16 * ks]));
-                fh[i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                    &Hs[buf][(wn * 128 + i * 32 + frow) * SLD + fk + 16 * ks]));
-                fl[i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(
-                    &Ls[buf][(wn * 128 + i * 32 + frow) * SLD + fk + 16 * ks]));
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] = mfma32_bf16(fa[i], fh[j], acc[i][j]);
-                    acc[i][j] = mfma32_bf16(fa[i], fl[j], acc[i][j]);
-                }
-            __builtin_amdgcn_sched_barrier(0);   // one step's fragments live at a time
-        }
-    };
-    // One slab in flight in registers while the previous one is multiplied out
-    // of LDS (the prefetch runs across pass and block boundaries, in the order
-    // of the cursor).
-    Slab3 st;
-    gload(st);
-    lstore(st, 0);
-    __syncthreads();
-    for (int l = 0; l < n_blocks; ++l)
-        for (int ot = 0; ot < n_ot; ++ot) {
-            for (int k = 0; k < ns2; k += 2) {
-                gload(st);
-                compute(0);
-                lstore(st, 1);
-                __syncthreads();
-                gload(st);
-                compute(1);
-                lstore(st, 0);
-                __syncthreads();
-            }
-            fold_rows(acc, psum, lane);
-        }
-
-    finish_rows(psum, &rowsum[0][0][0], tid, lane, wm, wn, nrows, r0, self_out, rsqrt_out);
-}
-
 // ------------------------------------------------------------------------
-// bf16 gradients with D a multiple of 64: the same 256 x 256 tile per pass,
-// 4 waves x (4 x 4 32x32x16 MFMA blocks), with the operands copied straight
-// from memory into an LDS ring (gfx950 buffer_load ... lds), as in the score
-// GEMM.  The contraction of a pass runs over 2D columns of the interleaved W
-// (per 64-column chunk c: hi, then lo), one 64-column step at a time; the
-// gradients' 64 columns of chunk c serve both steps of the chunk, so a
-// gradient slab is copied once per two steps.  Ring: 2 gradient stages, 3 W
-// stages of 32 KB (256 rows of 128 bytes, chunk c of row r at position
-// c ^ ((r >> 1) & 7)).  Copies run two steps ahead: during the first step of
-// a chunk, the next chunk's gradient slab and the W slab two steps ahead;
-// during the second, the W slab two steps ahead.  One barrier per step, in
-// the middle of its last 16-wide MFMA group, after each wave has waited for
-// its own copies of the next step's slabs (vmcnt, which counts the copies).
+// bf16 gradients: a 256 x 256 tile per pass (gradients x outputs), 4 waves x
+// (4 x 4 32x32x16 MFMA blocks), with the operands copied straight from memory
+// into an LDS ring (gfx950 buffer_load ... lds), as in the score GEMM.  The
+// contraction of a pass runs over the interleaved W (per 64-column chunk c: hi,
+// then lo), one 64-column step at a time; the gradients' 64 columns of chunk c
+// serve both steps of the chunk, so a gradient slab is copied once per two
+// steps.  Ring: 2 gradient stages, 3 W stages of 32 KB (256 rows of 128 bytes,
+// chunk c of row r at position c ^ ((r >> 1) & 7)).  Copies run two steps
+// ahead: during the first step of a chunk, the next chunk's gradient slab and
+// the W slab two steps ahead; during the second, the W slab two steps ahead.
+// One barrier per step, in the middle of its last 16-wide MFMA group, after
+// each wave has waited for its own copies of the next step's slabs (vmcnt,
+// which counts the copies).
+//
+// W is lower triangular: pass ot needs chunks up to 4 ot + 3, and of its eight
+// 32-output blocks chunk 4 ot + d meets only those from 2 d on.  Wave column
+// wn takes blocks 0, 3, 4, 7 (wn = 0) or 1, 2, 5, 6, so that both have 4 - d of
+// them, the last ones: at D = 256, 20 of 32 products are formed.  The last
+// chunk of a D that is not a multiple of 64 is narrower; columns past it read
+// as zeros on both sides.
+//
+// blockIdx.y: one of gridDim.y ranges of blocks, whose sums go to
+// part[range][gradient] when there are several (k_self_influence_fold adds
+// them).  32,768 gradients are 128 workgroups, half the chip, without ranges.
+// Measured, 32,768 gradients of 224 blocks of 256: about 1.25 ms; 2,645 us with
+// all products and one range.
 constexpr int DBK = 64;                          // columns per step
 constexpr int kDSlab = 256 * DBK * 2;            // bytes of one operand slab
 constexpr int kDStA = 2, kDStB = 3;
@@ -263,7 +142,7 @@ constexpr int kDCopies = kDSlab / 1024 / 4;      // 1 KB copies per wave and ope
 
 __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *__restrict__ g, int64_t ld,
                                                                int64_t rows, int D, int n_blocks,
-                                                               const bf16_bits *__restrict__ w,
+                                                               const bf16_bits *__restrict__ w, float *part,
                                                                float *__restrict__ self_out,
                                                                float *__restrict__ rsqrt_out) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[kDLds];
@@ -276,9 +155,13 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
     const uint32_t lds0 = lds_addr(smem);
     const int n_ot = (D + SO - 1) / SO;
     const int Dp = n_ot * SO;
-    const int n_chunks = D / DBK;            // gradient slabs per pass (two W steps each)
-    const int n_steps = 2 * n_chunks;        // W steps per pass
+    const int n_chunks = (D + DBK - 1) / DBK;
     const uint32_t w_row = 2u * D * 2u;      // bytes per row of the interleaved W
+    // this workgroup's blocks
+    const uint32_t nb = n_blocks, range = blockIdx.y, ranges = gridDim.y;   // nb * ranges < 2^24
+    const int l0 = __builtin_amdgcn_readfirstlane(static_cast<int>(nb * range / ranges));
+    const int l1 = __builtin_amdgcn_readfirstlane(static_cast<int>(nb * (range + 1) / ranges));
+    auto chunks_of = [&](int ot) { return min(n_chunks, 4 * (ot + 1)); };
 
     // copy i of this wave covers rows rb + 8 i, rb = 64 wave + (l >> 3), of a
     // slab; lane l loads chunk (l & 7) ^ (((8 wave + i) * 4 + (l >> 4)) & 7) of
@@ -288,27 +171,29 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
     // past the last block, through a descriptor of size 0.
     const int rb = 64 * wave + (lane >> 3);
     uint32_t va[2], vb[2];
+    int cc[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int cc = 8 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7));
-        va[h] = static_cast<uint32_t>((rb * ld + cc) * 2);
-        vb[h] = static_cast<uint32_t>(rb) * w_row + static_cast<uint32_t>(cc) * 2u;
+        cc[h] = 8 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7));
+        va[h] = static_cast<uint32_t>((rb * ld + cc[h]) * 2);
+        vb[h] = static_cast<uint32_t>(rb) * w_row + static_cast<uint32_t>(cc[h]) * 2u;
     }
     const uint32_t a_bytes = static_cast<uint32_t>(nrows * ld * 2);
     const uint32_t a_step8 = static_cast<uint32_t>(8 * ld * 2), b_step8 = 8u * w_row;
     // issue cursors, advanced in the order the slabs are consumed: gradient
     // slab (al, aot, aj) and W step (bl, bot, bt) = (block, output pass, chunk
     // or step within the pass)
-    int al = 0, aot = 0, aj = 0, bl = 0, bot = 0, bt = 0;
-    auto rsrc_a = [&]() { return buf_rsrc_uniform(g + r0 * ld, al < n_blocks ? a_bytes : 0u); };
+    int al = l0, aot = 0, aj = 0, bl = l0, bot = 0, bt = 0;
+    auto rsrc_a = [&]() { return buf_rsrc_uniform(g + r0 * ld, al < l1 ? a_bytes : 0u); };
     auto issue_a = [&](const __amdgpu_buffer_rsrc_t &rsa, uint32_t lds, int i) {
-        const uint32_t dk = static_cast<uint32_t>((al * D + aj * DBK) * 2) + i * a_step8;
+        uint32_t dk = static_cast<uint32_t>((al * D + aj * DBK) * 2) + i * a_step8;
+        asm volatile("" : "+s"(dk));   // stays scalar: 16 hoisted vector sums would spill
         // the streamed gradients carry the non-temporal hint (1% faster on a 200,000-row
         // store; the same hint on the inverse-factor copies was slower)
-        copy_to_lds_nt(rsa, va[i & 1] + dk, lds + wave * kDCopies * 1024 + i * 1024);
+        copy_to_lds_nt(rsa, cc[i & 1] < D - aj * DBK ? va[i & 1] + dk : kBufOOB, lds + wave * kDCopies * 1024 + i * 1024);
     };
     auto next_a = [&]() {
-        if (++aj == n_chunks) {
+        if (++aj == chunks_of(aot)) {
             aj = 0;
             if (++aot == n_ot) {
                 aot = 0;
@@ -316,16 +201,20 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
             }
         }
     };
-    auto rsrc_b = [&]() {
-        const size_t blk = static_cast<size_t>(bl < n_blocks ? bl : 0) * Dp * 2 * D;
-        return buf_rsrc_uniform(w + blk, bl < n_blocks ? static_cast<uint32_t>(Dp) * w_row : 0u);
+    auto rsrc_b = [&]() {   // nothing past the last block, nor of rows whose outputs the step leaves out
+        const bool live = bl < l1 && wave >= (bt >> 1) - 4 * bot;
+        const size_t blk = static_cast<size_t>(bl < l1 ? bl : l0) * Dp * 2 * D;
+        return buf_rsrc_uniform(w + blk, live ? static_cast<uint32_t>(Dp) * w_row : 0u);
     };
     auto issue_b = [&](const __amdgpu_buffer_rsrc_t &rsb, uint32_t lds, int i) {
-        const uint32_t dk = static_cast<uint32_t>(bot * SO) * w_row + static_cast<uint32_t>(bt * DBK * 2) + i * b_step8;
-        copy_to_lds(rsb, vb[i & 1] + dk, lds + wave * kDCopies * 1024 + i * 1024);
+        const int width = min(DBK, D - (bt >> 1) * DBK);   // of the chunk
+        const uint32_t col = static_cast<uint32_t>((bt >> 1) * 2 * DBK + (bt & 1) * width);
+        uint32_t dk = static_cast<uint32_t>(bot * SO) * w_row + col * 2u + i * b_step8;
+        asm volatile("" : "+s"(dk));
+        copy_to_lds(rsb, cc[i & 1] < width ? vb[i & 1] + dk : kBufOOB, lds + wave * kDCopies * 1024 + i * 1024);
     };
     auto next_b = [&]() {
-        if (++bt == n_steps) {
+        if (++bt == 2 * chunks_of(bot)) {
             bt = 0;
             if (++bot == n_ot) {
                 bot = 0;
@@ -335,12 +224,14 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
     };
 
     // fragment byte offsets inside a slab: lane l reads row (l % 32) of each
-    // 32-row block, logical chunk 2 ks + (l / 32) at position chunk ^ sw
+    // 32-row block, logical chunk 2 ks + (l / 32) at position chunk ^ sw; the
+    // wave's output block j is 2 j + (j & 1 ^ wn)
     const int sw = (lane >> 1) & 7;
-    const uint32_t fa0 = (wm * 128 + (lane & 31)) * 128, fb0 = (wn * 128 + (lane & 31)) * 128;
     uint32_t fo[4];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) fo[ks] = static_cast<uint32_t>(((2 * ks + (lane >> 5)) ^ sw) * 16);
+    for (int ks = 0; ks < 4; ++ks)
+        fo[ks] = static_cast<uint32_t>((lane & 31) * 128 + ((2 * ks + (lane >> 5)) ^ sw) * 16);
+    const int ua = wm * 128 * 128, ub[2] = {wn * 4096, (1 - wn) * 4096};   // wave-uniform parts
 
     Acc acc;
     float psum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -350,22 +241,24 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
     auto ldfrag1 = [&](int f, const uint8_t *abase, const uint8_t *bbase, int ks, int q) {
         const int i = q >> 1;
         if (q & 1)
-            fb[f][i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(bbase + fb0 + fo[ks] + i * 4096));
+            fb[f][i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(bbase + ub[i & 1] + fo[ks] + 2 * i * 4096));
         else
-            fa[f][i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(abase + fa0 + fo[ks] + i * 4096));
-    };
-    auto mfma1 = [&](int f, int idx) {
-        const int i = idx >> 2, j = idx & 3;
-        acc[i][j] = mfma32_bf16(fa[f][i], fb[f][j], acc[i][j]);
+            fa[f][i] = as_bf16x8(*reinterpret_cast<const u32x4 *>(abase + ua + fo[ks] + i * 4096));
     };
 
     // One step: W slab t (stage sb) against the gradient slab of its chunk
     // (stage sa).  FIRST (first step of a chunk): also copies the next
     // gradient slab, into the other A stage, whose previous slab was last
-    // read in the step before this one.
+    // read in the step before this one.  J0: the first of the wave's output
+    // blocks that the chunk meets.
     int sa = 0, sb = 0;
-    auto step = [&](auto first_tag) {
+    auto step = [&](auto first_tag, auto j0_tag) {
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int J0 = decltype(j0_tag)::value;
+        auto mfma1 = [&](int f, int idx) {
+            const int i = idx >> 2, j = idx & 3;
+            if (j >= J0) acc[i][j] = mfma32_bf16(fa[f][i], fb[f][j], acc[i][j]);
+        };
         const uint8_t *abase = smem + sa * kDSlab, *bbase = smem + kDLdsB + sb * kDSlab;
         const int nb1 = sb == 2 ? 0 : sb + 1;   // stage of W step t + 1
         const int nb2 = sb == 0 ? 2 : sb - 1;   // stage of W step t + 2 (held step t - 1)
@@ -407,6 +300,10 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
         sa = na;
         sb = nb1;
     };
+    auto chunk = [&](auto j0_tag) {
+        step(std::integral_constant<bool, true>(), j0_tag);
+        step(std::integral_constant<bool, false>(), j0_tag);
+    };
 
     {   // prologue: gradient slab 0, W steps 0 and 1
         const auto rsa0 = rsrc_a();
@@ -425,22 +322,39 @@ __global__ __launch_bounds__(STH, 1) void k_self_influence_dma(const bf16_bits *
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(kDCopies) : "memory");
 #pragma unroll
     for (int q = 0; q < 8; ++q) ldfrag1(0, smem, smem + kDLdsB, 0, q);
-    for (int l = 0; l < n_blocks; ++l)
+    for (int l = l0; l < l1; ++l)
         for (int ot = 0; ot < n_ot; ++ot) {
-            for (int c = 0; c < n_chunks; ++c) {
-                step(std::integral_constant<bool, true>());
-                step(std::integral_constant<bool, false>());
-            }
+            // as loops of 0 or 1 passes: branches around the steps would copy the accumulators
+            const int diag = chunks_of(ot) - 4 * ot;   // 1 .. 4
+            const int n0 = 4 * ot + 1, n1 = min(diag / 2, 1), n2 = min(diag / 3, 1), n3 = diag / 4;
+            for (int c = 0; c < n0; ++c) chunk(std::integral_constant<int, 0>());
+            for (int c = 0; c < n1; ++c) chunk(std::integral_constant<int, 1>());
+            for (int c = 0; c < n2; ++c) chunk(std::integral_constant<int, 2>());
+            for (int c = 0; c < n3; ++c) chunk(std::integral_constant<int, 3>());
             fold_rows(acc, psum, lane);
         }
     // the copies past the last block are still in flight
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    finish_rows(psum, reinterpret_cast<float *>(smem), tid, lane, wm, wn, nrows, r0, self_out, rsqrt_out);
+    if (gridDim.y > 1)
+        finish_rows(psum, reinterpret_cast<float *>(smem), tid, lane, wm, wn, nrows, r0, part + blockIdx.y * rows, nullptr);
+    else
+        finish_rows(psum, reinterpret_cast<float *>(smem), tid, lane, wm, wn, nrows, r0, self_out, rsqrt_out);
 }
 
-// Any D (and fp32 gradients): one workgroup per gradient; thread d forms
-// output d of W_l g_l with the hi + lo halves (all D columns), a fixed-order
-// block sum adds the squares, blocks in order.  For small problems.
+// The sums of the ranges of blocks, in order.
+__global__ __launch_bounds__(256) void k_self_influence_fold(const float *__restrict__ part, int64_t rows, int ranges,
+                                                             float *__restrict__ self_out, float *__restrict__ rsqrt_out) {
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (j >= rows) return;
+    float sv = part[j];
+    for (int r = 1; r < ranges; ++r) sv += part[r * rows + j];
+    if (self_out) self_out[j] = sv;
+    if (rsqrt_out) rsqrt_out[j] = sv > 0.f ? 1.0f / sqrtf(sv) : 0.f;
+}
+
+// fp32 gradients: one workgroup per gradient; thread d forms output d of W_l g_l
+// with the hi + lo halves (all D columns), a fixed-order block sum adds the
+// squares, blocks in order.  For small problems.
 template <typename TIn>
 __global__ __launch_bounds__(256) void k_self_influence_rows(const TIn *__restrict__ g, int64_t ld, int D,
                                                              int n_blocks, const bf16_bits *__restrict__ w_hi,
@@ -485,17 +399,29 @@ hipError_t launch_self_influence(const void *g, bool bf16, int64_t ld, int64_t r
     if (rows == 0) return hipSuccess;
     void *w = const_cast<void *>(ws);
     const bf16_bits *hi = self_influence_w(w, D, n_blocks, false), *lo = self_influence_w(w, D, n_blocks, true);
-    if (self_influence_interleaved(bf16, D)) {
-        const unsigned grid = static_cast<unsigned>((rows + SR - 1) / SR);
-        hipLaunchKernelGGL(k_self_influence_dma, dim3(grid), dim3(STH), 0, s, static_cast<const bf16_bits *>(g),
-                           ld, rows, D, n_blocks, hi, self_out, rsqrt_out);
-    } else if (bf16 && D % SK == 0) {
-        const unsigned grid = static_cast<unsigned>((rows + SR - 1) / SR);
-        hipLaunchKernelGGL(k_self_influence, dim3(grid), dim3(STH), 0, s, static_cast<const bf16_bits *>(g), ld,
-                           rows, D, n_blocks, hi, lo, self_out, rsqrt_out);
-    } else if (bf16) {
-        hipLaunchKernelGGL(k_self_influence_rows<bf16_bits>, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
-                           static_cast<const bf16_bits *>(g), ld, D, n_blocks, hi, lo, self_out, rsqrt_out);
+    if (self_influence_interleaved(bf16)) {
+        // Ranges of blocks, so that the last round of workgroups is full: the
+        // rounds times the blocks of a range plus one (the fill and the fold),
+        // at its least; as many as fit in the preconditioner's solutions, which
+        // are no longer needed.
+        const int64_t wgs = (rows + SR - 1) / SR;
+        size_t room = 0;
+        float *part = self_influence_part(w, D, n_blocks, &room);
+        int ranges = 1;
+        int64_t best = 0;
+        for (int r = 1; r <= n_blocks && r <= 256; ++r) {
+            if (r > 1 && static_cast<size_t>(r) * rows * sizeof(float) > room) break;
+            const int64_t cost = ((wgs * r + 255) / 256) * ((n_blocks + r - 1) / r + 1);
+            if (r == 1 || cost < best) {
+                best = cost;
+                ranges = r;
+            }
+        }
+        hipLaunchKernelGGL(k_self_influence_dma, dim3(static_cast<unsigned>(wgs), static_cast<unsigned>(ranges)), dim3(STH),
+                           0, s, static_cast<const bf16_bits *>(g), ld, rows, D, n_blocks, hi, part, self_out, rsqrt_out);
+        if (ranges > 1)
+            hipLaunchKernelGGL(k_self_influence_fold, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0, s, part,
+                               rows, ranges, self_out, rsqrt_out);
     } else {
         hipLaunchKernelGGL(k_self_influence_rows<float>, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
                            static_cast<const float *>(g), ld, D, n_blocks, hi, lo, self_out, rsqrt_out);
