@@ -138,6 +138,14 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
     return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
 }
 
+// 1 / sqrt(x) to about an ulp: the hardware estimate (relative error below
+// 2^-20) and one third-order step.
+__device__ __forceinline__ double rsqrt_d(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double h = fma(-x * y, y, 1.0);
+    return fma(y * h, fma(h, 0.375, 0.5), y);
+}
+
 __device__ __forceinline__ f32x4 mfma16_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }

@@ -36,20 +36,21 @@
 //   largest magnitude (lowest index among equal magnitudes) is positive.
 //
 //  Q and Z are kept in row quads (four rows of a column adjacent).
-//  2. k_cq_dma / k_cq_regs (+ k_cq_sum): Z = C Q; a workgroup owns 64 rows
-//     of C (32 for p > 64) and a range of its columns, its waves splitting
-//     the range; 16x16x4 fp32 MFMAs.  p <= 64 (bound by the reads of C):
-//     64-column slabs of C and Q copied into an LDS ring; wider: 128-bit
-//     loads into a register pipeline.  Column ranges (splits) give about
-//     2048 workgroups; their partials are summed in split order.
-//  3. k_gram_part: fp64 partial sums of X^T Y over 64-row chunks (X^T X for
-//     the orthonormalisation, Z^T Q for Rayleigh-Ritz), fixed order.
-//  4. k_chol_inv_cols (one workgroup): the chunk sums (summed on the chip
-//     first by k_sum_parts), a shifted Cholesky Z^T Z + eps tr/p I =
-//     R^T R and R^{-1} in fp64, columns in registers and each step's row
-//     broadcast through LDS (p <= 64: one wave; wider: four waves, one
-//     barrier per step).
-//  5. k_apply_rinv: Q = Z R^{-1} (fp64 arithmetic, fp32 result).
+//  2. k_cq_dma / k_cq_regs: Z = C Q; a workgroup owns 64 rows of C (32 for
+//     p > 64) and a range of its columns, its waves splitting the range;
+//     16x16x4 fp32 MFMAs.  p <= 64 (bound by the reads of C): 64-column slabs
+//     of C and Q copied into an LDS ring; wider: 128-bit loads into a register
+//     pipeline.  Column ranges (splits, at most 8 below n = 4,608) spread
+//     small C over the chip; the next kernel sums their partials in order.
+//  3. k_gram_mfma (p <= 64; k_cq_sum and k_gram_part above): fp64 partial sums
+//     of X^T Y over chunks of rows (X^T X for the orthonormalisation, Z^T Q
+//     for Rayleigh-Ritz), fixed order.
+//  4. p <= 32: k_chol_apply: every workgroup sums the chunks, forms the shifted
+//     Cholesky Z^T Z + eps tr/p I = R^T R and R^{-1} in fp64 in one wave, and
+//     applies it to its rows, Q = Z R^{-1} (fp64 arithmetic, fp32 result).
+//  5. p > 32: k_sum_parts, k_chol_inv_cols (one workgroup: columns in registers
+//     and each step's row broadcast through LDS; p <= 64: one wave; wider: four
+//     waves, one barrier per step), k_apply_rinv.
 //  6. k_jacobi_rot (one workgroup): T in LDS, round-robin parallel cyclic
 //     Jacobi (m/2 disjoint rotations per round, each round one pass of 2 x 2
 //     blocks), the rotations logged; k_jacobi_replay: W^T = the logged
@@ -857,12 +858,150 @@ __global__ __launch_bounds__(256) void k_gram_part(const float *__restrict__ X, 
     }
 }
 
-void launch_gram(const float *X, const float *Y, int n, int p, int pp, double *part, hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>((round4(n) + kGramRows - 1) / kGramRows),
-                    static_cast<unsigned>((p * p + 4095) / 4096));
-    if (pp <= 32) hipLaunchKernelGGL(k_gram_part<32>, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
-    else if (pp <= 64) hipLaunchKernelGGL(k_gram_part<64>, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
-    else hipLaunchKernelGGL(k_gram_part<128>, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
+// Rows per Gram partial: 64-row chunks for the wide subspaces of k_gram_part, a
+// step or two of the eight waves of k_gram_mfma otherwise.
+__host__ __device__ constexpr int gram_rows(int pp) { return pp <= 32 ? 256 : pp <= 64 ? 128 : kGramRows; }
+
+// The same partial sums for p <= 64 on the fp64 matrix cores, over chunks of
+// gram_rows(pp) rows.  Eight waves take 16 rows each at a time: lane (c, q) loads
+// rows 4 q .. 4 q + 3 of column c of each 16-column block (one 128-bit load;
+// row 4 q + t goes to the t-th MFMA of a step, for both operands), and the
+// waves' sums are folded through LDS in fixed order.  Y may still be in
+// `splits` partials (splits > 1, at Ys, a distance of n4 pp apart): they are
+// added in fp64, rounded once and also written to Y.  SAME: X is Y.
+// Measured, n = 768 to 3,072, p = 32, 6 to 8 splits: 7.0-7.7 us with 256-row chunks; a thread per output
+// over 64-row chunks staged in LDS took 6.1 after a 4.2 us sum of the splits.
+template <int NB, bool SAME>
+__global__ __launch_bounds__(512) void k_gram_mfma(const float *__restrict__ X, const float *__restrict__ Ys,
+                                                   float *__restrict__ Y, int n, int p, int splits,
+                                                   double *__restrict__ part) {
+    constexpr int pp = 16 * NB;
+    __shared__ f64x4 fold[4][NB * NB][kWave];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int nq = round4(n) / 4;                       // row quads
+    const size_t per_split = static_cast<size_t>(nq) * pp;   // 128-bit elements
+    const f32x4 *X4 = reinterpret_cast<const f32x4 *>(X), *Y4 = reinterpret_cast<const f32x4 *>(Ys);
+    f64x4 acc[NB][NB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+    constexpr int kSteps = gram_rows(pp) / 128;   // of 16 rows a wave; their loads go together
+    size_t at[kSteps];
+    bool in[kSteps];
+    f32x4 x[kSteps][NB], y[kSteps][NB];
+    f64x4 sum[kSteps][NB];   // of the splits
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const int quad = (static_cast<int>(blockIdx.x) * gram_rows(pp) + 128 * u + 16 * wave) / 4 + q;
+        in[u] = quad < nq;
+        at[u] = static_cast<size_t>(in[u] ? quad : 0) * pp + c;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            sum[u][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+            if (!SAME) x[u][b] = X4[at[u] + 16 * b];
+        }
+    }
+    constexpr int kBatch = NB <= 2 ? 8 : 2;   // splits whose loads go together
+    for (int t0 = 0; t0 < splits; t0 += kBatch) {
+        f32x4 v[kBatch][kSteps][NB];
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t)
+            if (t0 + t < splits) {
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) v[t][u][b] = Y4[(t0 + t) * per_split + at[u] + 16 * b];
+            }
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t)
+            if (t0 + t < splits) {
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) sum[u][b] += __builtin_convertvector(v[t][u][b], f64x4);
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) y[u][b] = __builtin_convertvector(sum[u][b], f32x4);
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (splits > 1 && in[u]) reinterpret_cast<f32x4 *>(Y)[at[u] + 16 * b] = y[u][b];
+            y[u][b] = in[u] ? y[u][b] : f32x4{0.f, 0.f, 0.f, 0.f};
+            if (SAME) x[u][b] = y[u][b];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[a][b] = mfma16_f64(static_cast<double>(x[u][a][t]), static_cast<double>(y[u][b][t]), acc[a][b]);
+    }
+#pragma unroll
+    for (int half = 4; half >= 1; half >>= 1) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) fold[wave - half][a * NB + b][lane] = acc[a][b];
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] += fold[wave][a * NB + b][lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {   // register t of lane (c, q): row q + 4 t of block a, column c of block b
+        double *dst = part + static_cast<size_t>(blockIdx.x) * p * p;
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int i = 16 * a + q + 4 * t, j = 16 * b + c;
+                    if (i < p && j < p) dst[i * p + j] = acc[a][b][t];
+                }
+    }
+}
+
+inline int gram_chunks(int n, int pp) { return (round4(n) + gram_rows(pp) - 1) / gram_rows(pp); }
+
+// Partial sums of X^T Y; Y is the sum of `splits` partials at Ys (and written) when there are several.
+void launch_gram(const float *X, const float *Ys, float *Y, int splits, int n, int p, int pp, double *part, hipStream_t s) {
+    if (pp <= 64) {
+        const dim3 grid(static_cast<unsigned>(gram_chunks(n, pp)));
+        auto go = [&](auto nb) {
+            constexpr int NB = decltype(nb)::value;
+            if (X == Y)
+                hipLaunchKernelGGL((k_gram_mfma<NB, true>), grid, dim3(512), 0, s, X, Ys, Y, n, p, splits, part);
+            else
+                hipLaunchKernelGGL((k_gram_mfma<NB, false>), grid, dim3(512), 0, s, X, Ys, Y, n, p, splits, part);
+        };
+        switch (pp / 16) {
+            case 1: return go(std::integral_constant<int, 1>());
+            case 2: return go(std::integral_constant<int, 2>());
+            case 3: return go(std::integral_constant<int, 3>());
+            default: return go(std::integral_constant<int, 4>());
+        }
+    }
+    if (splits > 1) {
+        const int64_t nv = static_cast<int64_t>(round4(n)) * pp / 4;
+        hipLaunchKernelGGL(k_cq_sum, dim3(static_cast<unsigned>((nv + 255) / 256)), dim3(256), 0, s,
+                           reinterpret_cast<const f32x4 *>(Ys), nv, splits, reinterpret_cast<f32x4 *>(Y));
+    }
+    const dim3 grid(static_cast<unsigned>(gram_chunks(n, pp)), static_cast<unsigned>((p * p + 4095) / 4096));
+    hipLaunchKernelGGL(k_gram_part<128>, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
 }
 
 // G = sum of the chunk partials, in chunk order, into A (all threads).  The
@@ -1077,54 +1216,161 @@ __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict_
 }
 
 void launch_chol_inv(const double *part, int chunks, int p, double *RinvT, hipStream_t s) {
-    if (p <= 32) hipLaunchKernelGGL(k_chol_inv_cols<32>, dim3(1), dim3(256), 0, s, part, chunks, p, RinvT);
-    else if (p <= 64) hipLaunchKernelGGL(k_chol_inv_cols<64>, dim3(1), dim3(256), 0, s, part, chunks, p, RinvT);
+    if (p <= 64) hipLaunchKernelGGL(k_chol_inv_cols<64>, dim3(1), dim3(256), 0, s, part, chunks, p, RinvT);
     else hipLaunchKernelGGL(k_chol_inv_cols<kMaxP>, dim3(1), dim3(256), 0, s, part, chunks, p, RinvT);
 }
 
-// Q = Z R^{-1} in row quads.  Lane = one row quad, wave = four consecutive
-// columns j0 .. j0 + 3: entry (i, j) = sum over m <= j of Z[i][m]
-// R^{-1}[m][j] in fp64 (fp32 result), m ascending.  R^{-1} comes transposed
-// (column j a contiguous row, zero past the diagonal), so the four columns
-// share one loop to j0 + 3, the entries past a column's diagonal adding exact
-// zeros; its entries are the same across the wave (scalar loads), and each
-// 128-bit load of Z feeds 16 FMAs.  The padding columns j >= p are zero.
-__global__ __launch_bounds__(256) void k_apply_rinv(const float *__restrict__ Z, int n, int p, int pp,
-                                                    const double *__restrict__ RinvT, float *__restrict__ Q) {
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-    const int lane = threadIdx.x & 63;
-    const int j0 = 4 * (4 * static_cast<int>(blockIdx.y) + wave);
-    const int64_t nq = round4(n) / 4;
-    const int64_t quad = static_cast<int64_t>(blockIdx.x) * kWave + lane;
-    const bool qin = quad < nq;
-    double acc[4][4];   // [column j0 + u][row 4 quad + r]
+// Q = Z R^{-1} in row quads, on the fp64 matrix cores (fp32 result): a wave owns
+// 16 rows and computes Q^T = R^{-T} Z^T, one 16-column block of Q at a time,
+// over m up to the block's last column (R^{-1} is upper triangular).  Lane
+// (i, q) has R^{-T}[16 b + i][m] and Z[i][m], m = 4 s + q, for the s-th MFMA;
+// four lanes of a quad and four m are 64 contiguous bytes of Z, and so is what a
+// store covers.  The padding columns j >= p come out as zeros.
+template <int NB>
+struct ApplyRows {
+    static constexpr int pp = 16 * NB;
+    int row;
+    bool in;
+    float z[4 * NB];
+    __device__ __forceinline__ ApplyRows(const float *__restrict__ Z, int n, int lane, int wave) {
+        const int n4 = round4(n);
+        row = (static_cast<int>(blockIdx.x) * 4 + wave) * 16 + (lane & 15);
+        in = row < n4;
+        const float *Zr = Z + qidx(in ? row : 0, 0, pp);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+        for (int s = 0; s < 4 * NB; ++s) z[s] = Zr[4 * (4 * s + (lane >> 4))];
+    }
+    // rinv(j, m): R^{-T}[j][m], zero where j or m is p or more
+    template <typename F>
+    __device__ __forceinline__ void store(F rinv, int lane, float *__restrict__ Q) const {
+        const int i = lane & 15, q = lane >> 4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[u][r] = 0.0;
-    if (j0 < p) {
-        const f32x4 *Z4 = reinterpret_cast<const f32x4 *>(Z) + (qin ? quad : 0) * pp;
-        const int mend = min(j0 + 4, p);
-        const double *R[4];
+        for (int b = 0; b < NB; ++b) {
+            double rv[4 * NB];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) R[u] = RinvT + static_cast<size_t>(min(j0 + u, p - 1)) * p;
-#pragma unroll 4
-        for (int m = 0; m < mend; ++m) {
-            const f32x4 z = Z4[m];
+            for (int s = 0; s < 4 * (b + 1); ++s) rv[s] = rinv(16 * b + i, 4 * s + q);
+            f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const double rv = j0 + u < p ? R[u][m] : 0.0;
+            for (int s = 0; s < 4 * (b + 1); ++s) acc = mfma16_f64(rv[s], static_cast<double>(z[s]), acc);
+            if (in) {   // register t of lane (i, q): column 16 b + q + 4 t, row i
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[u][r] = fma(static_cast<double>(z[r]), rv, acc[u][r]);
+                for (int t = 0; t < 4; ++t) Q[qidx(row, 16 * b + q + 4 * t, pp)] = static_cast<float>(acc[t]);
             }
         }
     }
-    if (!qin) return;
-    f32x4 *Q4 = reinterpret_cast<f32x4 *>(Q) + quad * pp + j0;
+};
+
+template <int NB>
+__global__ __launch_bounds__(256) void k_apply_rinv(const float *__restrict__ Z, int n, int p,
+                                                    const double *__restrict__ RinvT, float *__restrict__ Q) {
+    const int lane = threadIdx.x & 63;
+    const ApplyRows<NB> rows(Z, n, lane, __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6));
+    rows.store(
+        [&](int j, int m) {
+            const double v = RinvT[j < p && m < p ? j * p + m : 0];
+            return j < p && m < p ? v : 0.0;
+        },
+        lane, Q);
+}
+
+// For p <= 32 (padded with the identity to PM = 16 NB) every workgroup of the
+// apply makes R^{-T} itself, from at most kCholChunks Gram partials, in one
+// wave: lanes 0 .. PM - 1 hold the rows of G + shift, lanes PM .. 2 PM -
+// 1 those of the identity, and the elimination that makes the former L = R^T
+// makes the latter R^{-1}.  Step j scales column j by the reciprocal root of
+// its pivot (by readlane) and subtracts it from the later columns, the one that
+// the next pivot waits for first.  Bound by that chain of p pivots (13 us with
+// every factor by readlane: two of them and an FMA, 6 cycles each, 496 times).
+// Measured, n = 768 to 3,072, p = 32: 12 us; a launch for the Cholesky in column
+// form with back substitution took 21.2, the sum of 48 partials before it 3.3
+// and a lane per row quad with fp64 FMAs after it 7.2.
+constexpr int kCholChunks = 12;
+__device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }   // v has its value here
+template <int NB>
+__global__ __launch_bounds__(256) void k_chol_apply(const double *__restrict__ part, int chunks, const float *__restrict__ Z,
+                                                    int n, int p, float *__restrict__ Q) {
+    constexpr int PM = 16 * NB, RS = PM + 2;
+    static_assert(PM == 16 || PM == 32, "two matrices of PM rows in one wave");
+    __shared__ double A[PM * PM];
+    __shared__ double Rt[PM * RS];   // R^{-T}
+    __shared__ __attribute__((aligned(16))) double bc[2][PM];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const ApplyRows<NB> rows(Z, n, lane, wave);
+    {
+        constexpr int kPer = PM * PM / 256;
+        double v[kPer][kCholChunks];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        Q4[u] = f32x4{static_cast<float>(acc[u][0]), static_cast<float>(acc[u][1]), static_cast<float>(acc[u][2]),
-                      static_cast<float>(acc[u][3])};
+        for (int u = 0; u < kPer; ++u)   // all loads in flight; absent partials read the last one
+#pragma unroll
+            for (int c = 0; c < kCholChunks; ++c)
+                v[u][c] = part[static_cast<size_t>(min(c, chunks - 1)) * p * p + min(tid + 256 * u, p * p - 1)];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            double g = v[u][0];
+#pragma unroll
+            for (int c = 1; c < kCholChunks; ++c) g += c < chunks ? v[u][c] : 0.0;
+            if (tid + 256 * u < p * p) A[tid + 256 * u] = g;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        double tr = lane < p ? A[lane * p + lane] : 0.0;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) tr += __shfl_xor(tr, o, kWave);
+        const double shift = 1e-12 * (tr > 0.0 ? tr / p : 1.0);
+        const int row = lane & (PM - 1);
+        double x[PM];
+#pragma unroll
+        for (int k = 0; k < PM; ++k) {   // G is symmetric: row `row` read as a column
+            const double g = A[min(k, p - 1) * p + min(row, p - 1)];
+            const double v = row < p && k < p ? (row == k ? g + shift : g) : row == k ? 1.0 : 0.0;
+            x[k] = lane < PM ? v : row == k ? 1.0 : 0.0;
+        }
+        auto root = [](double d) { return rsqrt_d(d > 0.0 ? d : 1.0); };   // a non-positive pivot cannot follow the shift
+        double inv = root(readlane_d(x[0], 0));
+        static_for<PM>([&](auto step) __attribute__((always_inline)) {
+            constexpr int j = decltype(step)::value;
+            x[j] *= inv;
+            if constexpr (j + 1 < PM) {
+                // column j through LDS (a wave's LDS operations keep their order), two values a
+                // broadcast read, except the one that the next pivot waits for
+                double *col = bc[j & 1];
+                if (lane < PM) col[row] = x[j];
+                constexpr int k0 = (j + 2) & ~1, kPairs = (PM - k0) / 2;
+                double2 l[kPairs > 0 ? kPairs : 1];
+#pragma unroll
+                for (int t = 0; t < kPairs; ++t) l[t] = *reinterpret_cast<const double2 *>(col + k0 + 2 * t);
+                __builtin_amdgcn_sched_barrier(0);
+                x[j + 1] = fma(-x[j], readlane_d(x[j], j + 1), x[j + 1]);
+                const double piv = readlane_d(x[j + 1], j + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                inv = root(piv);
+                static_for<PM - j - 2>([&](auto t) __attribute__((always_inline)) {
+                    constexpr int k = j + 2 + decltype(t)::value;
+                    x[k] = fma(-x[j], (k & 1) ? l[(k - k0) / 2].y : l[(k - k0) / 2].x, x[k]);
+                });
+                // made here: sunk towards their readers, the updates would keep every value read alive
+                static_for<PM - j - 2>([&](auto t) __attribute__((always_inline)) {
+                    constexpr int k = j + 2 + decltype(t)::value;
+                    pin(x[k]);
+                });
+            }
+        });
+        if (lane >= PM && lane < 2 * PM) {   // row m of R^{-1} is column m of R^{-T}
+#pragma unroll
+            for (int k = 0; k < PM; ++k) Rt[k * RS + row] = row < p && k < p ? x[k] : 0.0;
+        }
+    }
+    __syncthreads();
+    rows.store([&](int j, int m) { return Rt[j * RS + m]; }, lane, Q);
+}
+
+// 1 / x to about an ulp: the hardware estimate and one third-order step.
+__device__ __forceinline__ double rcp_d(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double h = fma(-x, y, 1.0);
+    return fma(y * h, 1.0 + h, y);
 }
 
 // One workgroup: T = (sum of the chunk partials of Q^T Z), symmetrised, is
@@ -1196,11 +1442,13 @@ __global__ __launch_bounds__(256) void k_jacobi_rot(const double *__restrict__ p
                 }
                 double c = 1.0, sv = 0.0;
                 if (b < p) {
-                    const double apq = T[a * p + b];
-                    if (apq != 0.0) {
-                        const double tau = (T[b * p + b] - T[a * p + a]) / (2.0 * apq);
-                        const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                        c = 1.0 / sqrt(1.0 + t * t);
+                    // t = sign(d) x / (|d| + sqrt(d^2 + x^2)), the smaller root, with x = 2 T_ab and d =
+                    // T_bb - T_aa; values whose squares vanish (T is of fp32 size) are left alone
+                    const double x = 2.0 * T[a * p + b], d = T[b * p + b] - T[a * p + a];
+                    const double r2 = fma(d, d, x * x);
+                    if (x != 0.0 && r2 > 1e-280) {
+                        const double t = (d >= 0.0 ? x : -x) * rcp_d(fabs(d) + r2 * rsqrt_d(r2));
+                        c = rsqrt_d(fma(t, t, 1.0));
                         sv = t * c;
                     }
                 }
@@ -1451,7 +1699,6 @@ inline int pca_p(int n, int k) {
     return w < n ? w : n;
 }
 inline int pca_pp(int n, int k) { return (pca_p(n, k) + 15) / 16 * 16; }
-inline int gram_chunks(int n) { return (round4(n) + kGramRows - 1) / kGramRows; }
 inline size_t block_floats(int n, int pp) { return static_cast<size_t>(round4(n)) * pp; }
 inline size_t rot_bytes(int p) {
     const int m = p + (p & 1);
@@ -1465,7 +1712,11 @@ inline int cq_mr(int pp) { return pp / 16 <= 4 ? 4 : 2; }
 inline int cq_kr(int n, int pp) {
     const int rb = (n + 16 * cq_mr(pp) - 1) / (16 * cq_mr(pp));
     int sp = (2048 + rb - 1) / rb;
-    sp = sp < n / 512 ? sp : n / 512;
+    // at least 512 columns each, or 128 while there are no more than 8: a split
+    // costs the sum another read of n p values, and n = 768 in one piece is 12
+    // workgroups (9 us a pass; 4.5 in six)
+    const int most = n / 512 > 8 ? n / 512 : n / 128 < 8 ? n / 128 : 8;
+    sp = sp < most ? sp : most;
     sp = sp > 1 ? sp : 1;
     return ((n + sp - 1) / sp + 63) / 64 * 64;
 }
@@ -1483,7 +1734,7 @@ PcaLayout pca_layout(void *ws, int n, int k) {
     L.Zs = sp > 1 ? reinterpret_cast<float *>(w) : L.Z;
     w += sp > 1 ? align256(sizeof(float) * block_floats(n, pp) * sp) : 0;
     L.part = reinterpret_cast<double *>(w);
-    w += align256(sizeof(double) * static_cast<size_t>(gram_chunks(n)) * p * p);
+    w += align256(sizeof(double) * static_cast<size_t>(gram_chunks(n, pp)) * p * p);
     L.RinvT = reinterpret_cast<double *>(w);
     w += align256(sizeof(double) * static_cast<size_t>(p) * p);
     L.Wt = reinterpret_cast<double *>(w);
@@ -1507,7 +1758,8 @@ void launch_cq_nb(const float *C, int n, const float *Q, float *Zs, hipStream_t 
         hipLaunchKernelGGL((k_cq_regs<NB, MR>), grid, dim3(256), 0, s, C, n, Q, kr, Zs);
 }
 
-hipError_t launch_cq(const PcaLayout &L, const float *C, int n, int pp, const float *Q, float *Z, hipStream_t s) {
+// C Q into Z, or into the splits' partials at L.Zs when there are several (returns their number).
+int launch_cq(const PcaLayout &L, const float *C, int n, int pp, const float *Q, float *Z, hipStream_t s) {
     const int sp = cq_splits(n, pp);
     float *dst = sp > 1 ? L.Zs : Z;
     switch (pp / 16) {
@@ -1520,29 +1772,44 @@ hipError_t launch_cq(const PcaLayout &L, const float *C, int n, int pp, const fl
         case 7: launch_cq_nb<7>(C, n, Q, dst, s); break;
         default: launch_cq_nb<8>(C, n, Q, dst, s); break;
     }
-    if (sp > 1) {
-        const int64_t nv = static_cast<int64_t>(block_floats(n, pp) / 4);
-        hipLaunchKernelGGL(k_cq_sum, dim3(static_cast<unsigned>((nv + 255) / 256)), dim3(256), 0, s,
-                           reinterpret_cast<const f32x4 *>(L.Zs), nv, sp, reinterpret_cast<f32x4 *>(Z));
-    }
-    return hipGetLastError();
+    return sp;
 }
 
-// Sums the Gram partials on the chip; returns the chunk count left for the
-// one-workgroup kernel that follows.
+// Sums the Gram partials on the chip where they are too many for the
+// workgroups of the kernel that follows (more than kCholChunks of 32 x 32);
+// returns the chunk count left for it.
 int sum_parts(double *part, int chunks, int p, hipStream_t s) {
-    if (chunks == 1) return chunks;
+    if (chunks == 1 || (p <= 32 && chunks <= kCholChunks)) return chunks;
     hipLaunchKernelGGL(k_sum_parts, dim3(static_cast<unsigned>((p * p + kWave - 1) / kWave)), dim3(256), 0, s, part,
                        chunks, p * p);
     return 1;
 }
 
-// Q = orthonormalised Z (shifted CholQR)
-void cholqr(const PcaLayout &L, int n, int p, int pp, const float *Z, float *Q, hipStream_t s) {
-    launch_gram(Z, Z, n, p, pp, L.part, s);
-    launch_chol_inv(L.part, sum_parts(L.part, gram_chunks(n), p, s), p, L.RinvT, s);
-    const dim3 grid(static_cast<unsigned>((round4(n) / 4 + kWave - 1) / kWave), static_cast<unsigned>(pp / 16));
-    hipLaunchKernelGGL(k_apply_rinv, grid, dim3(256), 0, s, Z, n, p, pp, L.RinvT, Q);
+// Q = orthonormalised Z (shifted CholQR); Z still in `splits` partials at L.Zs when there are several
+void cholqr(const PcaLayout &L, int n, int p, int pp, float *Z, int splits, float *Q, hipStream_t s) {
+    launch_gram(Z, splits > 1 ? L.Zs : Z, Z, splits, n, p, pp, L.part, s);
+    const int chunks = sum_parts(L.part, gram_chunks(n, pp), p, s);
+    const dim3 grid(static_cast<unsigned>((round4(n) + 63) / 64));
+    if (pp == 16) {
+        hipLaunchKernelGGL(k_chol_apply<1>, grid, dim3(256), 0, s, L.part, chunks, Z, n, p, Q);
+        return;
+    }
+    if (pp == 32) {
+        hipLaunchKernelGGL(k_chol_apply<2>, grid, dim3(256), 0, s, L.part, chunks, Z, n, p, Q);
+        return;
+    }
+    launch_chol_inv(L.part, chunks, p, L.RinvT, s);
+    auto go = [&](auto nb) {
+        hipLaunchKernelGGL(k_apply_rinv<decltype(nb)::value>, grid, dim3(256), 0, s, Z, n, p, L.RinvT, Q);
+    };
+    switch (pp / 16) {
+        case 3: return go(std::integral_constant<int, 3>());
+        case 4: return go(std::integral_constant<int, 4>());
+        case 5: return go(std::integral_constant<int, 5>());
+        case 6: return go(std::integral_constant<int, 6>());
+        case 7: return go(std::integral_constant<int, 7>());
+        default: return go(std::integral_constant<int, 8>());
+    }
 }
 
 }  // namespace
@@ -1552,7 +1819,7 @@ size_t pca_ws_bytes(int n, int k) {
     const int sp = cq_splits(n, pp);
     return 2 * align256(sizeof(float) * block_floats(n, pp)) +
            (sp > 1 ? align256(sizeof(float) * block_floats(n, pp) * sp) : 0) +
-           align256(sizeof(double) * static_cast<size_t>(gram_chunks(n)) * p * p) +
+           align256(sizeof(double) * static_cast<size_t>(gram_chunks(n, pp)) * p * p) +
            2 * align256(sizeof(double) * static_cast<size_t>(p) * p) + align256(sizeof(double) * p) +
            align256(rot_bytes(p)) + align256(sizeof(int));
 }
@@ -1564,17 +1831,17 @@ hipError_t launch_pca_topk(const float *C, int n, int k, int iters, void *P, boo
     const unsigned g = static_cast<unsigned>((static_cast<int64_t>(block_floats(n, pp)) + 255) / 256);
     hipLaunchKernelGGL(k_pca_init, dim3(g), dim3(256), 0, s, L.Q, n, p, pp);
     for (int it = 0; it < iters; ++it) {
-        hipError_t e = launch_cq(L, C, n, pp, L.Q, L.Z, s);
+        const int sp = launch_cq(L, C, n, pp, L.Q, L.Z, s);
+        cholqr(L, n, p, pp, L.Z, sp, L.Q, s);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        cholqr(L, n, p, pp, L.Z, L.Q, s);
     }
     // second orthonormalisation (CholQR2) into Z, then Rayleigh-Ritz on the
     // basis Z: Q = C Z, T = Z^T Q
-    cholqr(L, n, p, pp, L.Q, L.Z, s);
-    hipError_t e = launch_cq(L, C, n, pp, L.Z, L.Q, s);
-    if (e != hipSuccess) return e;
-    launch_gram(L.Z, L.Q, n, p, pp, L.part, s);
-    const int chunks = sum_parts(L.part, gram_chunks(n), p, s);
+    cholqr(L, n, p, pp, L.Q, 1, L.Z, s);
+    const int sp = launch_cq(L, C, n, pp, L.Z, L.Q, s);
+    launch_gram(L.Z, sp > 1 ? L.Zs : L.Q, L.Q, sp, n, p, pp, L.part, s);
+    const int chunks = sum_parts(L.part, gram_chunks(n, pp), p, s);
     if (p <= 64)
         hipLaunchKernelGGL(k_jacobi_rot<64>, dim3(1), dim3(256), 0, s, L.part, chunks, p, L.rot, L.rounds, L.theta);
     else

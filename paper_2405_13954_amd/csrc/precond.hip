@@ -115,14 +115,6 @@ __global__ __launch_bounds__(256) void k_form(const TS *S, int D, int64_t N, con
     if (i == 0 && threadIdx.x == 0) info[blk] = 0;
 }
 
-// 1 / sqrt(x) to about an ulp: the hardware estimate (relative error below
-// 2^-20) and one third-order step.
-__device__ __forceinline__ double rsqrt_d(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double h = fma(-x * y, y, 1.0);
-    return fma(y * h, fma(h, 0.375, 0.5), y);
-}
-
 __device__ __forceinline__ f64x4 mma_unit(const double (&a)[4], const double (&b)[4], f64x4 c) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) c = mfma16_f64(a[i], b[i], c);

@@ -290,3 +290,33 @@ def test_act_cov_tile_orders(ns):
         single = torch.zeros_like(C)
         P.logra_act_cov_accumulate(a, single, mask=mask)
         assert torch.equal(single, want)
+
+
+@pytest.mark.parametrize("n,k", [(9, 3), (40, 16), (61, 9), (130, 16), (255, 5), (257, 12), (600, 20), (900, 24),
+                                 (1100, 32), (1290, 16), (2700, 11), (700, 40)])
+def test_pca_subspace_sizes(n, k):
+    """Subspace widths around 16, 32, 48 and 64 (each has its own orthonormalisation), row counts around the 64, 128
+    and 256 of the kernels' chunks, and one, a few and many column splits of C Q: the top-k of a matrix of known
+    decaying spectrum, against numpy's float64 eigenvectors.  Neighbouring eigenvalues differ by 20%, fp32 products by
+    about 1e-6 of the largest one: the last of k eigenvectors is off by 1e-6 / (0.2 decay^k) at most, here with a
+    decay chosen so that decay^k >= 0.02."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, host, say
+    decay = max(0.8, 0.02 ** (1.0 / k))
+    C = W.spectral_matrix(65 + n, n, decay, scale=3.0)
+    say(f"[pca sizes] n={n} k={k} p={min(n, max(2 * k, 16))} decay={decay:.3f}")
+    Pr = torch.zeros((k, n), device="cuda")
+    ev = torch.zeros(k, device="cuda")
+    P.logra_pca_topk(dev(C), k, Pr, ev, iters=60)
+    want_ev, want = np.linalg.eigh(C.astype(np.float64))
+    want_ev, want = want_ev[::-1][:k], want[:, ::-1][:, :k].T
+    got = host(Pr).astype(np.float64)
+    gap = 1.0 - decay
+    for e in range(k):
+        # the distance itself: 1 - dot^2 of fp32 rows would cancel to about sqrt(2^-24)
+        off = np.linalg.norm(got[e] - np.sign(got[e] @ want[e]) * want[e])
+        assert off <= 1e-6 / (gap * decay ** e) + 1e-6, (e, off)
+        assert got[e][np.argmax(np.abs(got[e]))] > 0
+    assert np.max(np.abs(host(ev) - want_ev) / want_ev[0]) <= 1e-5
+    assert np.max(np.abs(got @ got.T - np.eye(k))) <= 1e-5
