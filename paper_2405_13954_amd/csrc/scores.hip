@@ -444,61 +444,94 @@ __global__ __launch_bounds__(GT, 1) void k_scores_small(const bf16_bits *__restr
 }
 
 // fp32 / fp64 operands: every product and sum in float64 (a product of two
-// fp32 values is exact there), the result rounded once to fp32.  One 64 x 64
-// output tile per workgroup; 16-column slabs of both operands are staged
-// through LDS as float64 (coalesced row reads, transposed stores), and each
-// thread accumulates a 4 x 4 block over the whole contraction in order d =
-// 0, 1, ..., D-1.  Scales (normalised scores) multiply in float64 before the
-// rounding.
-constexpr int FT = 64, FK = 16;
-template <typename TA, typename TB>
+// fp32 values is exact there), on the fp64 matrix cores, the result rounded
+// once to fp32.  A workgroup owns 16 F queries x 16 F train rows; its four waves
+// split the columns into contiguous bands of 16-column units, loaded one unit
+// ahead (lane (r, q) reads columns 2 q, 2 q + 1, 2 q + 8, 2 q + 9 of a unit of
+// row r, for the four MFMAs of the unit, of both operands), and the four
+// partial tiles are added in fixed order through LDS.  Scales (normalised
+// scores) multiply in float64 before the rounding.  F: the largest tile that
+// still gives every CU a workgroup.  Bound by latency at the sizes of fp32
+// workloads: 8 x 32 rows of 1,024 columns 14 us; 130 in a 64 x 64 tile of scalar
+// FMAs.
+template <int F, typename TA, typename TB>
 __global__ __launch_bounds__(256) void k_scores_f64acc(const TA *te, int64_t ld_te, int Q, const TB *tr,
                                                        int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s,
                                                        ScoreScale scale) {
-    __shared__ double As[FK][FT + 1];   // [column][query]
-    __shared__ double Bs[FK][FT + 1];   // [column][train row]
+    constexpr int FT = 16 * F;
+    __shared__ double part[4][FT][FT + 1];
     const int q0 = blockIdx.y * FT;
     const int64_t j0 = static_cast<int64_t>(blockIdx.x) * FT;
-    const int tid = threadIdx.x, ta = tid >> 4, tb = tid & 15;
-    double acc[4][4] = {};
-    for (int k0 = 0; k0 < D; k0 += FK) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+    const int nu = (D + 15) / 16, per = (nu + 3) / 4;
+    const int u0 = wave * per, u1 = min(nu, u0 + per);
+    const TA *pa[F];
+    const TB *pb[F];
 #pragma unroll
-        for (int u = 0; u < FT * FK / 256; ++u) {
-            const int e = tid + 256 * u, r = e / FK, c = e % FK, d = k0 + c;
-            const int q = q0 + r;
-            const int64_t j = j0 + r;
-            As[c][r] = (q < Q && d < D) ? load_in_d<TA>(te + static_cast<int64_t>(q) * ld_te + d) : 0.0;
-            Bs[c][r] = (j < N && d < D) ? load_in_d<TB>(tr + j * ld_tr + d) : 0.0;
-        }
-        __syncthreads();
+    for (int x = 0; x < F; ++x) {   // rows past the end: the last one, not stored
+        pa[x] = te + static_cast<int64_t>(min(q0 + 16 * x + r, Q - 1)) * ld_te;
+        const int64_t j = j0 + 16 * x + r;
+        pb[x] = tr + (j < N ? j : N - 1) * ld_tr;
+    }
+    f64x4 acc[F][F];
 #pragma unroll
-        for (int c = 0; c < FK; ++c) {
-            double x[4], y[4];
+    for (int x = 0; x < F; ++x)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                x[u] = As[c][4 * ta + u];
-                y[u] = Bs[c][tb + 16 * u];
+        for (int y = 0; y < F; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    TA a[2][F][4];
+    TB b[2][F][4];
+    auto load = [&](int buf, int u) {
+        const int k0 = 16 * u + 2 * q;
+        const bool whole = 16 * u + 16 <= D;   // the last unit reads its missing columns from the last one
+#pragma unroll
+        for (int x = 0; x < F; ++x)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int k = k0 + 8 * (t >> 1) + (t & 1), kc = whole || k < D ? k : D - 1;
+                a[buf][x][t] = pa[x][kc];
+                b[buf][x][t] = pb[x][kc];
+            }
+    };
+    auto mul = [&](int buf, int u) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const bool in = 16 * u + 2 * q + 8 * (t >> 1) + (t & 1) < D;   // and counts them as zero
+            double av[F], bv[F];
+#pragma unroll
+            for (int x = 0; x < F; ++x) {
+                av[x] = in ? static_cast<double>(a[buf][x][t]) : 0.0;
+                bv[x] = in ? static_cast<double>(b[buf][x][t]) : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int x = 0; x < F; ++x)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fma(x[u], y[v], acc[u][v]);
+                for (int y = 0; y < F; ++y) acc[x][y] = mfma16_f64(av[x], bv[y], acc[x][y]);
         }
-        __syncthreads();
+    };
+    if (u0 < u1) load(0, u0);
+    for (int u = u0; u < u1; u += 2) {
+        if (u + 1 < u1) load(1, u + 1);
+        mul(0, u);
+        if (u + 2 < u1) load(0, u + 2);
+        if (u + 1 < u1) mul(1, u + 1);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int q = q0 + 4 * ta + u;
-        if (q >= Q) continue;
+    for (int x = 0; x < F; ++x)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t j = j0 + tb + 16 * v;   // consecutive threads: consecutive columns
-            if (j >= N) continue;
-            double val = acc[u][v];
-            if (scale.row) val *= static_cast<double>(scale.row[q]);
-            if (scale.col) val *= static_cast<double>(scale.col[j]);
-            s[static_cast<int64_t>(q) * ld_s + j] = static_cast<float>(val);
-        }
+        for (int y = 0; y < F; ++y)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) part[wave][16 * x + q + 4 * t][16 * y + r] = acc[x][y][t];
+    __syncthreads();
+    for (int e = tid; e < FT * FT; e += 256) {
+        const int m = e / FT, c = e % FT;   // consecutive threads: consecutive columns
+        const int64_t j = j0 + c;
+        if (q0 + m >= Q || j >= N) continue;
+        double val = ((part[0][m][c] + part[1][m][c]) + part[2][m][c]) + part[3][m][c];
+        if (scale.row) val *= static_cast<double>(scale.row[q0 + m]);
+        if (scale.col) val *= static_cast<double>(scale.col[j]);
+        s[static_cast<int64_t>(q0 + m) * ld_s + j] = static_cast<float>(val);
     }
 }
 
@@ -859,13 +892,18 @@ hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const 
         }
     }
     if (filt || te_dt == kBF16 || tr_dt == kBF16) return hipErrorInvalidValue;   // bf16 pairs only with bf16
-    const dim3 grid(static_cast<unsigned>((N + FT - 1) / FT), static_cast<unsigned>((Q + FT - 1) / FT));
+    auto tiles = [&](int64_t t) { return (N + t - 1) / t * ((Q + t - 1) / t); };
+    const int f = tiles(64) >= 256 ? 4 : tiles(32) >= 256 ? 2 : 1;
+    const dim3 grid(static_cast<unsigned>((N + 16 * f - 1) / (16 * f)), static_cast<unsigned>((Q + 16 * f - 1) / (16 * f)));
     auto go = [&](auto a, auto b) {
         using TA = decltype(a);
         using TB = decltype(b);
-        hipLaunchKernelGGL((k_scores_f64acc<TA, TB>), grid, dim3(256), 0, st, static_cast<const TA *>(te), ld_te, Q,
-                           static_cast<const TB *>(tr), ld_tr, N, D, s, ld_s, scale);
-        return hipGetLastError();
+        auto run = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, static_cast<const TA *>(te), ld_te, Q,
+                               static_cast<const TB *>(tr), ld_tr, N, D, s, ld_s, scale);
+            return hipGetLastError();
+        };
+        return f == 4 ? run(k_scores_f64acc<4, TA, TB>) : f == 2 ? run(k_scores_f64acc<2, TA, TB>) : run(k_scores_f64acc<1, TA, TB>);
     };
     if (te_dt == kF64) return tr_dt == kF64 ? go(double{}, double{}) : go(double{}, float{});
     return tr_dt == kF64 ? go(float{}, double{}) : go(float{}, float{});

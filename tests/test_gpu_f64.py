@@ -118,3 +118,48 @@ def test_scores_f64_accumulation(te_dt, tr_dt, Q, N, D):
             nxt = wv[q, r + 1] if r + 1 < k else np.sort(want[q])[::-1][k] if N > k else -np.inf
             if wv[q, r] - nxt > 2 * bound[q].max():
                 assert gi[q, r] == wi[q, r]
+
+
+@pytest.mark.parametrize("te_dt,tr_dt,Q,N,D", [("f64", "f32", 1, 1, 1), ("f32", "f32", 15, 17, 15), ("f64", "f64", 17, 300, 17),
+                                               ("f32", "f64", 33, 9000, 50), ("f64", "f32", 130, 33, 257),
+                                               ("f32", "f32", 200, 5000, 40)])
+def test_scores_f64_tiles(te_dt, tr_dt, Q, N, D):
+    """The 16, 32 and 64 wide tiles of the float64 scores with remainders in rows and columns, strided operands, and
+    columns that the four bands do not share evenly: each score within half an fp32 ulp of the exact one plus the
+    float64 sum's own rounding."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, host, say
+    say(f"[scores f64 tiles] te={te_dt} tr={tr_dt} Q={Q} N={N} D={D}")
+    g = W.rng(57, Q, N, D)
+    te = W.normal(g, (Q, D + 4), 1.0, "f32").astype(np.float64 if te_dt == "f64" else np.float32)
+    tr = W.normal(g, (N, D + 4), 1.0, "f32").astype(np.float64 if tr_dt == "f64" else np.float32)
+    te[:, D:] = np.nan   # past the columns
+    tr[:, D:] = np.nan
+    s = torch.full((Q, N + 1), np.nan, dtype=torch.float32, device="cuda")
+    P.logra_influence_scores(dev(te)[:, :D], dev(tr)[:, :D], scores=s[:, :N])
+    got = host(s).astype(np.float64)
+    assert np.isnan(got[:, N]).all()
+    te, tr = np.ascontiguousarray(te[:, :D]), np.ascontiguousarray(tr[:, :D])
+    want = oracle.scores(te, tr)
+    bound = 2.0 ** -24 * np.abs(want) + 4 * D * 2.0 ** -53 * (np.abs(te.astype(np.float64)) @ np.abs(tr.astype(np.float64)).T)
+    assert (np.abs(got[:, :N] - want) <= bound).all()
+
+
+@pytest.mark.parametrize("B,D,nb,dt", [(1, 1, 2, "f32"), (31, 17, 3, "f64"), (32, 32, 1, "f32"), (33, 33, 2, "f32"),
+                                       (70, 100, 2, "f64"), (5, 256, 2, "f32")])
+def test_cov_f64_tile_edges(B, D, nb, dt):
+    """Widths around the 16 and 32 of a tile, batches around the 32 rows of a step; integer rows, so every sum is exact;
+    two calls accumulate."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, host, say
+    say(f"[cov f64 tiles] B={B} D={D} blocks={nb} {dt}")
+    g = W.integer_array(W.rng(58, B, D), (B, nb * D + 4), -50, 50, "f32")
+    g = g.astype(np.float64) if dt == "f64" else g
+    S = torch.zeros((nb, D, D), dtype=torch.float64, device="cuda")
+    for _ in range(2):
+        P.logra_cov_accumulate_f64(dev(g)[:, :nb * D], S, D)
+    got = host(S)
+    for l in range(nb):
+        assert np.array_equal(got[l], 2.0 * oracle.cov_accumulate(np.ascontiguousarray(g[:, l * D:(l + 1) * D])))
