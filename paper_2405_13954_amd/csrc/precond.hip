@@ -13,11 +13,11 @@
 //               W^T, to 16 or 32 right-hand sides per workgroup out of LDS.
 //   wider       k_lambda and k_form write A = C + lambda I (lower triangle);
 //               for each panel I: its factor (W_II over A's diagonal block),
-//               k_panel (L_JI = A_JI W_II^T), k_gemm (A_JK -= L_JI L_KI^T for
+//               k_panel (L_JI = A_JI W_II^T), k_trail_next (A_JK -= L_JI L_KI^T for
 //               the columns K of the next panel), k_trail_factor (the other
 //               columns, and the next factor beside them).
 //               Solve, forward: Y_I = W_II R_I (k_solve), R_J -= L_JI Y_I
-//               (k_gemm) for J > I; backward: Z_I = W_II^T Y_I, then
+//               (k_solve_gemm) for J > I; backward: Z_I = W_II^T Y_I, then
 //               Y_J -= L_IJ^T Z_I for J < I.
 //
 // So no step is a row-by-row recurrence except the 16 x 16 diagonal blocks
@@ -600,15 +600,8 @@ __global__ __launch_bounds__(256, 2) void k_panel(double *A_all, int D, int c0) 
     }
 }
 
-// C -= A_op B_op over the indices of the panel at c0 (256; fewer in a backward
-// step from the last panel: TAIL).  A wave has FX x FY blocks of 16 x 16, a
-// workgroup WX x WY waves.  Operands come straight from memory (an fp64 MFMA
-// runs 64 cycles, so a wave's loads of a unit, one unit ahead, fit easily),
-// contiguous along the contraction or across it; C is read before the first
-// product and only written at the end.  A 128 x 128 tile takes 54 us where its
-// MFMAs alone take 32; seven 4,096-wide layer blocks' trailing updates 5.1 ms
-// with the factors beside them (13.6 ms in 64-wide steps of scalar fp64 FMAs,
-// 3.9 + 1.8 one after the other).
+// C -= A_op B_op over the indices of the panel at c0: the trailing updates of
+// the factor and the block steps of the solves.
 constexpr int kTrailGroup = 6;
 enum GemmMode { kTrailNext, kTrailRest, kForward, kBackward };   // A_JK -= L_JI L_KI^T (two parts), the solves
 struct GemmArgs {
@@ -620,20 +613,30 @@ struct GemmArgs {
     int src;          // forward: where C's columns are (kFromIdent: zero from column c0 on)
 };
 
-template <int FX, int FY, int WX, int WY, int MODE, bool TAIL>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &p, int tile, int blk) {
+// Trailing update, A_JK -= L_JI L_KI^T for the tile `tile` of 16 FX WX rows and as
+// many columns.  A wave has FX x FY blocks of 16 x 16, a workgroup WX x WY waves.
+// A unit of the operands (16 contiguous indices of the tile's rows, then of its
+// columns' rows: 128 bytes each) is copied straight into a ring of three stages
+// in LDS, two units ahead, chunk c of row r at position c ^ ((r >> 1) & 7), so
+// that 16 lanes reading one chunk of 16 rows hit 16 banks; one barrier a unit.
+// (Fragments loaded from memory by each wave instead ask the CU for three times
+// the bytes, and it takes about 50 GB/s of such loads: 54 us a tile of 128 x 128
+// where its MFMAs take 32.)  C is read beside the last products.
+// Measured: seven 4,096-wide layer blocks' trailing updates 4.0 ms with the
+// factors beside them (5.1 with fragments from memory, 13.6 in 64-wide steps of
+// scalar fp64 FMAs).
+template <int FX, int FY, int WX, int WY, int MODE>
+__device__ __forceinline__ void trail_tile(const GemmArgs &p, int tile, int blk) {
+    constexpr int kTx = 16 * FX * WX, kWaves = WX * WY, kStages = 3;
+    constexpr int kStage = 2 * kTx * 128, kCopies = 2 * kTx / 8 / kWaves;   // bytes; 1 KB copies per wave and unit
+    static_assert(FX * WX == FY * WY, "the triangle is cut into squares");
+    __shared__ __attribute__((aligned(1024))) uint8_t ring[kStages * kStage];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kg = lane >> 4;
-    const int D = p.D;
+    const int D = p.D, base = p.c0 + PB;   // first row updated
     double *A = p.A + static_cast<size_t>(blk) * D * D;
-    double *Y = MODE == kTrailNext || MODE == kTrailRest ? nullptr : p.Y + static_cast<size_t>(blk) * D * p.Qp;
-    constexpr bool kTrail = MODE == kTrailNext || MODE == kTrailRest;
-    constexpr int kTx = 16 * FX * WX, kTy = 16 * FY * WY;
-    static_assert(!kTrail || kTx == kTy, "the triangle is cut into squares");
     int ti, tj;
-    const int base = MODE == kBackward ? 0 : p.c0 + PB;   // first row updated
-    const int rows_end = MODE == kBackward ? p.c0 : D, cols_end = kTrail ? D : p.Qp;
     constexpr int kW = PB / kTx;   // the next panel's columns are the first kW tile columns
     if (MODE == kTrailNext) {      // of the lower triangle of tiles, row by row
         constexpr int kTri = kW * (kW + 1) / 2;
@@ -641,7 +644,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &p, int tile, int blk) 
         if (tile < kTri)
             while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
         tj = tile < kTri ? tile - ti * (ti + 1) / 2 : (tile - kTri) % kW;
-    } else if (MODE == kTrailRest) {
+    } else {
         // The other tile columns: tile rows in groups of kTrailGroup, column by
         // column within a group, so that the 32 tiles an XCD has in hand at a
         // time share about 12 operand panels (3 MB, its L2) instead of 33.
@@ -654,94 +657,187 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &p, int tile, int blk) 
         ti += kW;
         tj += kW;
         if (base + ti * kTx >= D) return;
-    } else {
-        const int nq = p.src == kFromIdent && p.c0 + PB < p.Qp ? p.c0 + PB : p.Qp;
-        const int ntq = (nq + kTy - 1) / kTy;
-        tj = tile % ntq;
-        ti = tile / ntq;
     }
-    const int i0 = base + ti * kTx + 16 * FX * (wave / WY);
-    const int j0 = (kTrail ? base : 0) + tj * kTy + 16 * FY * (wave % WY);
+    const int it = base + ti * kTx, jt = base + tj * kTx;   // the tile's first row and column
+    const int wx = wave / WY, wy = wave % WY;
+
+    // copy i of this wave: stage rows 8 (kCopies wave + i) .. + 7, lane l chunk (l & 7) ^ ((row >> 1) & 7) of row l / 8
+    const auto rs = buf_rsrc_uniform(A, static_cast<uint32_t>(D) * D * 8u);
+    uint32_t off[kCopies];
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) {
+        const int r = 8 * (kCopies * wave + i) + (lane >> 3);
+        const int m = r < kTx ? it + r : jt + r - kTx;   // past D: the last row, not stored
+        off[i] = 8u * (static_cast<uint32_t>(m < D ? m : D - 1) * D + p.c0) + 16u * ((lane & 7) ^ ((r >> 1) & 7));
+    }
+    const uint32_t lds0 = lds_addr(ring) + kCopies * wave * 1024;
+    auto issue = [&](int u, int stage) {   // past the panel: a unit of the panel again, not used
+        const uint32_t du = 128u * (u < PB / FB ? u : 0);
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) copy_to_lds(rs, off[i] + du, lds0 + stage * kStage + i * 1024);
+    };
+    // a lane's two 16-byte chunks of a fragment row (rows 16 apart share the swizzle)
+    uint32_t fo[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) fo[h] = static_cast<uint32_t>(row * 128 + ((kg + 4 * h) ^ ((row >> 1) & 7)) * 16);
+    auto frag = [&](double (&v)[4], const uint8_t *blk16) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const double2 d = *reinterpret_cast<const double2 *>(blk16 + fo[h]);
+            v[2 * h] = d.x;
+            v[2 * h + 1] = d.y;
+        }
+    };
+    f64x4 acc[FX][FY];
+#pragma unroll
+    for (int x = 0; x < FX; ++x)
+#pragma unroll
+        for (int y = 0; y < FY; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    issue(0, 0);
+    issue(1, 1);
+    int cur = 0;
+    f64x4 c[FX][FY];
+    auto step = [&](int u) {
+        // this wave's copies of unit u are done when only the next unit's remain; after the barrier every
+        // wave's are, and every wave has read unit u - 1, whose stage the next copies refill
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(kCopies) : "memory");
+        issue(u + 2, cur == 0 ? 2 : cur - 1);
+        const uint8_t *st = ring + cur * kStage;
+        double a[FX][4], b[FY][4];
+#pragma unroll
+        for (int x = 0; x < FX; ++x) frag(a[x], st + (16 * FX * wx + 16 * x) * 128);
+#pragma unroll
+        for (int y = 0; y < FY; ++y) frag(b[y], st + (kTx + 16 * FY * wy + 16 * y) * 128);
+        mma_units(a, b, acc);
+        cur = cur == 2 ? 0 : cur + 1;
+    };
+    for (int u = 0; u < PB / FB - 1; ++u) step(u);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the compiler's own loads follow
+    const int i0 = it + 16 * FX * wx, j0 = jt + 16 * FY * wy;
+#pragma unroll
+    for (int x = 0; x < FX; ++x)
+#pragma unroll
+        for (int y = 0; y < FY; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
+                c[x][y][q] = A[static_cast<size_t>(i < D ? i : D - 1) * D + (j < D ? j : D - 1)];
+            }
+    {   // the last unit: no more copies
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const uint8_t *st = ring + cur * kStage;
+        double a[FX][4], b[FY][4];
+#pragma unroll
+        for (int x = 0; x < FX; ++x) frag(a[x], st + (16 * FX * wx + 16 * x) * 128);
+#pragma unroll
+        for (int y = 0; y < FY; ++y) frag(b[y], st + (kTx + 16 * FY * wy + 16 * y) * 128);
+        mma_units(a, b, acc);
+    }
+#pragma unroll
+    for (int x = 0; x < FX; ++x)
+#pragma unroll
+        for (int y = 0; y < FY; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
+                if (i < D && j < D) A[static_cast<size_t>(i) * D + j] = c[x][y][q] - acc[x][y][q];
+            }
+}
+
+template <int FX, int FY, int WX, int WY>
+__global__ __launch_bounds__(64 * WX * WY, 2) void k_trail_next(GemmArgs p) {
+    trail_tile<FX, FY, WX, WY, kTrailNext>(p, blockIdx.x, blockIdx.y);
+}
+
+// Block step of a solve in tiles of 64 rows x 64 right-hand sides, four waves of
+// 2 x 2 blocks of 16 x 16 (TAIL: a backward step from a panel narrower than 256).
+// Operands come straight from memory, one unit ahead; C is read beside the last
+// products.
+template <int MODE, bool TAIL>
+__global__ __launch_bounds__(256, 2) void k_solve_gemm(GemmArgs p) {
+    constexpr int F = 2, kT = 64;
+    const int blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kg = lane >> 4;
+    const int D = p.D;
+    const double *A = p.A + static_cast<size_t>(blk) * D * D;
+    double *Y = p.Y + static_cast<size_t>(blk) * D * p.Qp;
+    const int base = MODE == kBackward ? 0 : p.c0 + PB;   // first row updated
+    const int rows_end = MODE == kBackward ? p.c0 : D;
+    const int nq = p.src == kFromIdent && p.c0 + PB < p.Qp ? p.c0 + PB : p.Qp, ntq = (nq + kT - 1) / kT;
+    const int i0 = base + static_cast<int>(blockIdx.x / ntq) * kT + 32 * (wave >> 1);
+    const int j0 = static_cast<int>(blockIdx.x % ntq) * kT + 32 * (wave & 1);
     // operands: a wave-uniform base that moves along the contraction, and a
-    // lane's byte offset from it (32 bits where rows of A are meant: A is at most 512 MB)
-    const int64_t sa = MODE == kBackward ? D : 1, sb = kTrail ? 1 : p.Qp;   // step of the contraction index
+    // lane's byte offset from it (32 bits in A, which is at most 512 MB)
+    const int64_t sa = MODE == kBackward ? D : 1, sb = p.Qp;   // step of the contraction index
     const double *base_a = MODE == kBackward ? A + static_cast<size_t>(p.c0) * D : A + p.c0;
-    const double *base_b = kTrail ? A + p.c0 : Y + static_cast<size_t>(p.c0) * p.Qp;
-    using OffB = std::conditional_t<kTrail, uint32_t, size_t>;   // Y's rows may be long
-    uint32_t oa[FX];
-    OffB ob[FY];
+    const double *base_b = Y + static_cast<size_t>(p.c0) * p.Qp;
+    uint32_t oa[F];
+    size_t ob[F];
 #pragma unroll
-    for (int x = 0; x < FX; ++x) {
+    for (int x = 0; x < F; ++x) {
         const int i = i0 + 16 * x + row, ic = i < rows_end ? i : rows_end - 1;
+        const int j = j0 + 16 * x + row, jc = j < p.Qp ? j : p.Qp - 1;
         oa[x] = 8u * (MODE == kBackward ? 2u * kg * D + ic : static_cast<uint32_t>(ic) * D + 2u * kg);
-    }
-#pragma unroll
-    for (int y = 0; y < FY; ++y) {
-        const int j = j0 + 16 * y + row, jc = j < cols_end ? j : cols_end - 1;
-        ob[y] = 8u * (kTrail ? static_cast<OffB>(jc) * D + 2u * kg : static_cast<OffB>(2u * kg) * p.Qp + jc);
+        ob[x] = 8u * (static_cast<size_t>(2 * kg) * p.Qp + jc);
     }
     const int kn = TAIL ? D - p.c0 : PB;   // indices of the panel
     auto at = [](const double *from, auto off) {
         return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(from) + off);
     };
-    double a[2][FX][4], b[2][FY][4];
+    double a[2][F][4], b[2][F][4];
     auto load = [&](int buf, int u) {
         const double *ba = base_a + FB * u * sa, *bb = base_b + FB * u * sb;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const bool in = !TAIL || FB * u + 2 * kg + kx(t) < kn;
 #pragma unroll
-            for (int x = 0; x < FX; ++x) a[buf][x][t] = in ? -at(ba + kx(t) * sa, oa[x]) : 0.0;
-#pragma unroll
-            for (int y = 0; y < FY; ++y) b[buf][y][t] = in ? at(bb + kx(t) * sb, ob[y]) : 0.0;
+            for (int x = 0; x < F; ++x) {
+                a[buf][x][t] = in ? at(ba + kx(t) * sa, oa[x]) : 0.0;
+                b[buf][x][t] = in ? at(bb + kx(t) * sb, ob[x]) : 0.0;
+            }
         }
     };
-    load(0, 0);
-    f64x4 acc[FX][FY];
+    auto c_value = [&](int x, int y, int q) {   // rows and columns past the end: the last one's
+        const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
+        const int ic = i < rows_end ? i : rows_end - 1, jc = j < p.Qp ? j : p.Qp - 1;
+        if (MODE == kForward && p.src == kFromG)
+            return j < p.Q ? load_any(p.g, p.in_dt, j * p.ld_in + static_cast<int64_t>(blk) * D + ic) : 0.0;
+        if (MODE == kForward && p.src == kFromIdent && j >= p.c0) return 0.0;
+        return Y[static_cast<size_t>(ic) * p.Qp + jc];
+    };
+    f64x4 acc[F][F], c[F][F];
 #pragma unroll
-    for (int x = 0; x < FX; ++x)
+    for (int x = 0; x < F; ++x)
 #pragma unroll
-        for (int y = 0; y < FY; ++y)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
-                const int ic = i < rows_end ? i : rows_end - 1, jc = j < cols_end ? j : cols_end - 1;
-                double v;
-                if (kTrail)
-                    v = A[static_cast<size_t>(ic) * D + jc];
-                else if (MODE == kForward && p.src == kFromG)
-                    v = j < p.Q ? load_any(p.g, p.in_dt, j * p.ld_in + static_cast<int64_t>(blk) * D + ic) : 0.0;
-                else if (MODE == kForward && p.src == kFromIdent && j >= p.c0)
-                    v = 0.0;
-                else
-                    v = Y[static_cast<size_t>(ic) * p.Qp + jc];
-                acc[x][y][q] = v;
-            }
+        for (int y = 0; y < F; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
     const int nu = TAIL ? (kn + FB - 1) / FB : PB / FB;
-    for (int u = 0; u < nu; u += 2) {
-        if (u + 1 < nu) load(1, u + 1);
+    load(0, 0);
+    int u = 0;
+    for (; u + 2 < nu; u += 2) {
+        load(1, u + 1);
         mma_units(a[0], b[0], acc);
-        if (u + 2 < nu) load(0, u + 2);
-        if (u + 1 < nu) mma_units(a[1], b[1], acc);
+        load(0, u + 2);
+        mma_units(a[1], b[1], acc);
     }
+    if (u + 1 < nu) load(1, u + 1);
+    mma_units(a[0], b[0], acc);
 #pragma unroll
-    for (int x = 0; x < FX; ++x)
+    for (int x = 0; x < F; ++x)
 #pragma unroll
-        for (int y = 0; y < FY; ++y)
+        for (int y = 0; y < F; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[x][y][q] = c_value(x, y, q);
+    if (u + 1 < nu) mma_units(a[1], b[1], acc);
+#pragma unroll
+    for (int x = 0; x < F; ++x)
+#pragma unroll
+        for (int y = 0; y < F; ++y)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
-                if (i >= rows_end || j >= cols_end) continue;
-                if (kTrail)
-                    A[static_cast<size_t>(i) * D + j] = acc[x][y][q];
-                else
-                    Y[static_cast<size_t>(i) * p.Qp + j] = acc[x][y][q];
+                if (i < rows_end && j < p.Qp) Y[static_cast<size_t>(i) * p.Qp + j] = c[x][y][q] - acc[x][y][q];
             }
-}
-
-template <int FX, int FY, int WX, int WY, int MODE, bool TAIL>
-__global__ __launch_bounds__(64 * WX * WY, 2) void k_gemm(GemmArgs p) {
-    gemm_tile<FX, FY, WX, WY, MODE, TAIL>(p, blockIdx.x, blockIdx.y);
 }
 
 // The rest of a trailing update beside the factor of the next panel, which only
@@ -757,7 +853,7 @@ __global__ __launch_bounds__(kFactorThreads, 2) void k_trail_factor(GemmArgs p, 
     }
     const int per = (n_blocks * slots + 7) / 8, n = (b & 7) * per + (b >> 3);
     if ((b >> 3) >= per || n >= n_blocks * slots) return;
-    gemm_tile<4, 2, 2, 4, kTrailRest, false>(p, n % slots, n / slots);
+    trail_tile<4, 2, 2, 4, kTrailRest>(p, n % slots, n / slots);
 }
 
 __global__ __launch_bounds__(256) void k_clear_info(int *info, int n) {
@@ -815,15 +911,15 @@ hipError_t launch_solve_block(const SolveArgs &p, int cols, int n_blocks, hipStr
     return nc == 2 ? go(k_solve<16, 2>) : go(k_solve<16, 1>);
 }
 
-// One k_gemm launch of a solve, in 64 x 64 tiles.
+// One k_solve_gemm launch, in 64 x 64 tiles.
 template <int MODE>
 hipError_t launch_solve_gemm(const GemmArgs &p, int rows, int cols, int n_blocks, hipStream_t s) {
     const int64_t tiles = static_cast<int64_t>((rows + 63) / 64) * ((cols + 63) / 64);
     const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(n_blocks));
     if (MODE == kBackward && p.D - p.c0 < PB)
-        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, MODE, MODE == kBackward>), grid, dim3(256), 0, s, p);
+        hipLaunchKernelGGL((k_solve_gemm<MODE, MODE == kBackward>), grid, dim3(256), 0, s, p);
     else
-        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, MODE, false>), grid, dim3(256), 0, s, p);
+        hipLaunchKernelGGL((k_solve_gemm<MODE, false>), grid, dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
@@ -836,9 +932,9 @@ hipError_t launch_trail(const GemmArgs &p, int rest, int n_blocks, int *info, hi
         return r < w ? r * (r + 1) / 2 : w * (w + 1) / 2 + (r - w) * w;
     };
     if (next(128) * n_blocks >= 256)
-        hipLaunchKernelGGL((k_gemm<4, 2, 2, 4, kTrailNext, false>), dim3(next(128), n_blocks), dim3(512), 0, s, p);
+        hipLaunchKernelGGL((k_trail_next<4, 2, 2, 4>), dim3(next(128), n_blocks), dim3(512), 0, s, p);
     else
-        hipLaunchKernelGGL((k_gemm<2, 2, 2, 2, kTrailNext, false>), dim3(next(64), n_blocks), dim3(256), 0, s, p);
+        hipLaunchKernelGGL((k_trail_next<2, 2, 2, 2>), dim3(next(64), n_blocks), dim3(256), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int r = (rest + 127) / 128 - PB / 128, groups = r > 0 ? (r + kTrailGroup - 1) / kTrailGroup : 0;
