@@ -791,11 +791,17 @@ __global__ __launch_bounds__(64 * WX * WY, 2) void k_trail_next(GemmArgs p) {
 
 // Block step of a solve in tiles of 64 rows x 64 right-hand sides, four waves of
 // 2 x 2 blocks of 16 x 16 (TAIL: a backward step from a panel narrower than 256).
-// Operands come straight from memory, one unit ahead; C is read beside the last
-// products.
+// The ring of trail_tile, of units of 16 KB, three workgroups a CU: forward L's
+// rows as there, backward (L^T) and for the right-hand sides 16 rows of the
+// contraction, 64 columns each, whose two 128-byte halves of each 256 change
+// places in every other pair of rows (lanes 16 apart read rows two apart).
+// C is read beside the last products.
+// Measured: seven 4,096-wide layer blocks, 256 right-hand sides: 1.38 ms for the
+// 30 steps (1.59 with each wave's operands fetched into registers).
 template <int MODE, bool TAIL>
-__global__ __launch_bounds__(256, 2) void k_solve_gemm(GemmArgs p) {
-    constexpr int F = 2, kT = 64;
+__global__ __launch_bounds__(256, 3) void k_solve_gemm(GemmArgs p) {
+    constexpr int F = 2, kT = 64, kStages = 3, kStage = 2 * 8192;
+    __shared__ __attribute__((aligned(1024))) uint8_t ring[kStages * kStage];
     const int blk = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kg = lane >> 4;
@@ -803,41 +809,88 @@ __global__ __launch_bounds__(256, 2) void k_solve_gemm(GemmArgs p) {
     const double *A = p.A + static_cast<size_t>(blk) * D * D;
     double *Y = p.Y + static_cast<size_t>(blk) * D * p.Qp;
     const int base = MODE == kBackward ? 0 : p.c0 + PB;   // first row updated
-    const int rows_end = MODE == kBackward ? p.c0 : D;
+    const int rows_end = MODE == kBackward ? p.c0 : D;    // backward: a multiple of kT
     const int nq = p.src == kFromIdent && p.c0 + PB < p.Qp ? p.c0 + PB : p.Qp, ntq = (nq + kT - 1) / kT;
-    const int i0 = base + static_cast<int>(blockIdx.x / ntq) * kT + 32 * (wave >> 1);
-    const int j0 = static_cast<int>(blockIdx.x % ntq) * kT + 32 * (wave & 1);
-    // operands: a wave-uniform base that moves along the contraction, and a
-    // lane's byte offset from it (32 bits in A, which is at most 512 MB)
-    const int64_t sa = MODE == kBackward ? D : 1, sb = p.Qp;   // step of the contraction index
-    const double *base_a = MODE == kBackward ? A + static_cast<size_t>(p.c0) * D : A + p.c0;
-    const double *base_b = Y + static_cast<size_t>(p.c0) * p.Qp;
-    uint32_t oa[F];
-    size_t ob[F];
-#pragma unroll
-    for (int x = 0; x < F; ++x) {
-        const int i = i0 + 16 * x + row, ic = i < rows_end ? i : rows_end - 1;
-        const int j = j0 + 16 * x + row, jc = j < p.Qp ? j : p.Qp - 1;
-        oa[x] = 8u * (MODE == kBackward ? 2u * kg * D + ic : static_cast<uint32_t>(ic) * D + 2u * kg);
-        ob[x] = 8u * (static_cast<size_t>(2 * kg) * p.Qp + jc);
-    }
+    const int it = base + static_cast<int>(blockIdx.x / ntq) * kT, jt = static_cast<int>(blockIdx.x % ntq) * kT;
+    const int i0 = it + 32 * (wave >> 1), j0 = jt + 32 * (wave & 1);
     const int kn = TAIL ? D - p.c0 : PB;   // indices of the panel
-    auto at = [](const double *from, auto off) {
-        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(from) + off);
-    };
-    double a[2][F][4], b[2][F][4];
-    auto load = [&](int buf, int u) {
-        const double *ba = base_a + FB * u * sa, *bb = base_b + FB * u * sb;
+    const int nu = TAIL ? (kn + FB - 1) / FB : PB / FB;
+
+    // A wave's copies of a unit, 1 KB each: two of either operand.  Rows of the contraction: its rows 2 n and
+    // 2 n + 1, n = 2 wave + i, of 64 columns from `from`; past D the last row, which is masked (TAIL).
+    const uint32_t lds0 = lds_addr(ring) + wave * 2048;
+    auto copy_rows = [&](const double *from, int ld, int u, uint32_t lds) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const bool in = !TAIL || FB * u + 2 * kg + kx(t) < kn;
-#pragma unroll
-            for (int x = 0; x < F; ++x) {
-                a[buf][x][t] = in ? at(ba + kx(t) * sa, oa[x]) : 0.0;
-                b[buf][x][t] = in ? at(bb + kx(t) * sb, ob[x]) : 0.0;
-            }
+        for (int i = 0; i < 2; ++i) {
+            const int k = FB * u + 4 * wave + 2 * i, kc = TAIL && k >= kn ? kn - 1 : k;
+            const int second = TAIL && kc + 1 >= kn ? 0 : lane >> 5;
+            const auto rs = buf_rsrc_uniform(from + static_cast<size_t>(kc) * ld, 8u * ld + 512u);
+            copy_to_lds(rs, 8u * ld * second + 16u * ((lane & 31) ^ (8 * i)), lds + i * 1024);
         }
     };
+    const auto rs_l = buf_rsrc_uniform(A, static_cast<uint32_t>(D) * D * 8u);
+    uint32_t off[2];   // forward: rows of L, 128 bytes each, as in trail_tile
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 16 * wave + 8 * i + (lane >> 3), m = it + r < D ? it + r : D - 1;
+        off[i] = 8u * (static_cast<uint32_t>(m) * D + p.c0) + 16u * ((lane & 7) ^ ((r >> 1) & 7));
+    }
+    auto issue = [&](int u, int stage) {   // past the panel: a unit of the panel again, not used
+        u = u < nu ? u : 0;
+        const uint32_t lds = lds0 + stage * kStage;
+        if (MODE == kBackward) {
+            copy_rows(A + static_cast<size_t>(p.c0) * D + it, D, u, lds);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) copy_to_lds(rs_l, off[i] + 128u * u, lds + i * 1024);
+        }
+        copy_rows(Y + static_cast<size_t>(p.c0) * p.Qp + jt, p.Qp, u, lds + 8192);
+    };
+    uint32_t fo[2];   // a lane's two chunks of a fragment row of L
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+        fo[h] = static_cast<uint32_t>((32 * (wave >> 1) + row) * 128 + ((kg + 4 * h) ^ ((row >> 1) & 7)) * 16);
+    auto frag_rows = [&](double (&v)[4], const uint8_t *op, int n, int left) {   // columns n.., of which `left` indices count
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const double d = *reinterpret_cast<const double *>(op + kg * 1024 + kx(t) * 512 + ((8 * (n + row)) ^ (128 * (kg & 1))));
+            v[t] = 2 * kg + kx(t) < left ? d : 0.0;
+        }
+    };
+    f64x4 acc[F][F], c[F][F];
+#pragma unroll
+    for (int x = 0; x < F; ++x)
+#pragma unroll
+        for (int y = 0; y < F; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    int cur = 0;
+    auto products = [&](int left) {
+        const uint8_t *st = ring + cur * kStage;
+        double a[F][4], b[F][4];
+#pragma unroll
+        for (int x = 0; x < F; ++x) {
+            if (MODE == kBackward) {
+                frag_rows(a[x], st, 32 * (wave >> 1) + 16 * x, left);
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double2 d = *reinterpret_cast<const double2 *>(st + fo[h] + 2048 * x);
+                    a[x][2 * h] = d.x;
+                    a[x][2 * h + 1] = d.y;
+                }
+            }
+            frag_rows(b[x], st + 8192, 32 * (wave & 1) + 16 * x, left);
+        }
+        mma_units(a, b, acc);
+    };
+    issue(0, 0);
+    issue(1, 1);
+    for (int u = 0; u < nu - 1; ++u) {
+        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // as in trail_tile
+        issue(u + 2, cur == 0 ? 2 : cur - 1);
+        products(FB);
+        cur = cur == 2 ? 0 : cur + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the compiler's own loads follow
     auto c_value = [&](int x, int y, int q) {   // rows and columns past the end: the last one's
         const int i = i0 + 16 * x + kg + 4 * q, j = j0 + 16 * y + row;
         const int ic = i < rows_end ? i : rows_end - 1, jc = j < p.Qp ? j : p.Qp - 1;
@@ -846,29 +899,14 @@ __global__ __launch_bounds__(256, 2) void k_solve_gemm(GemmArgs p) {
         if (MODE == kForward && p.src == kFromIdent && j >= p.c0) return 0.0;
         return Y[static_cast<size_t>(ic) * p.Qp + jc];
     };
-    f64x4 acc[F][F], c[F][F];
-#pragma unroll
-    for (int x = 0; x < F; ++x)
-#pragma unroll
-        for (int y = 0; y < F; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
-    const int nu = TAIL ? (kn + FB - 1) / FB : PB / FB;
-    load(0, 0);
-    int u = 0;
-    for (; u + 2 < nu; u += 2) {
-        load(1, u + 1);
-        mma_units(a[0], b[0], acc);
-        load(0, u + 2);
-        mma_units(a[1], b[1], acc);
-    }
-    if (u + 1 < nu) load(1, u + 1);
-    mma_units(a[0], b[0], acc);
 #pragma unroll
     for (int x = 0; x < F; ++x)
 #pragma unroll
         for (int y = 0; y < F; ++y)
 #pragma unroll
             for (int q = 0; q < 4; ++q) c[x][y][q] = c_value(x, y, q);
-    if (u + 1 < nu) mma_units(a[1], b[1], acc);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    products(TAIL ? kn - FB * (nu - 1) : FB);
 #pragma unroll
     for (int x = 0; x < F; ++x)
 #pragma unroll
