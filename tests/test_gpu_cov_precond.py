@@ -224,7 +224,8 @@ def test_precondition_not_pd():
     (8, 3, 1, "f32", "f64"), (16, 2, 17, "f64", "f64"), (17, 1, 65, "f32", "f32"), (63, 2, 16, "bf16", "f64"),
     (65, 2, 33, "f32", "f64"), (129, 3, 5, "f32", "f64"), (255, 2, 64, "f64", "bf16"), (256, 300, 3, "bf16", "f64"),
     (256, 5, 1000, "f32", "f64"), (257, 2, 5, "f32", "f64"), (300, 1, 70, "bf16", "f32"), (512, 2, 129, "f64", "f64"),
-    (777, 2, 9, "f32", "f64"), (1024, 4, 64, "f32", "f64"), (1288, 1, 200, "bf16", "f64")])
+    (777, 2, 9, "f32", "f64"), (1000, 24, 7, "f32", "f64"), (1024, 4, 64, "f32", "f64"),
+    (1288, 1, 200, "bf16", "f64")])
 def test_precondition_panel_edges(D, nb, Q, idt, odt):
     """Widths around the 16-wide blocks, the 256-wide panels and their remainders, numbers of right-hand sides around
     the 16, 32 and 64 of a workgroup, and both solve paths.  A float64 solve of a system of condition number kappa is
