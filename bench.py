@@ -1035,7 +1035,7 @@ def relatif_sub_leg(args, torch, P, S, Nc, damp, pre, train, topk, sws, tv, ti):
         if timed:
             scaled_t.stop(e0)
     torch.cuda.synchronize()
-    flops = 4.0 * N * nb * D * D
+    flops = 2.0 * N * nb * D * (D + 1)   # two bf16 products with a triangle
     tf = flops / (self_t.mean_ms() * 1e-3) / 1e12
     traffic, ratio = measured_traffic("self_influence", SELF_SOURCES)
     return {"self_influence_ms": self_t.mean_ms(), "scaled_scores_topk_ms": scaled_t.mean_ms(),
