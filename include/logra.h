@@ -257,6 +257,9 @@ int logra_precondition_f64(const double *S, int D, int n_blocks, int64_t N, doub
  * candidates (up to 8192 per query), and the candidates are merged; a query
  * whose candidates overflow is selected from its full score row.  The result
  * is the same exact top-k in every case.
+ * The order of a bf16 score's fp32 sum depends on Q, N_chunk and D (and, in a
+ * long chunk, on whether the row is in the prefix), so a row scored within a
+ * chunk of another length may differ in its last bits.
  * N_chunk < 2^31; for bf16, ld_te and ld_tr < 2^22.
  * Scores of NaN order unspecified.
  * ---------------------------------------------------------------------- */
@@ -318,7 +321,8 @@ int logra_influence_scores_scaled(const void *g_test_pre, int te_dtype, int64_t 
  * copy stream while chunk c - 1 is scored on `stream` (events order the
  * reuse of the two buffers).  topk_val / topk_idx [Q][topk] (device) get the
  * top-k over all N rows with global indices 0..N-1, exactly as one
- * logra_influence_scores call over the whole store would give them (N = 0:
+ * logra_influence_scores call over the whole store would give them, bit for
+ * bit (each row's sums take the order of that call whatever the chunks; N = 0:
  * padding).  copy_stream: a hipStream_t of the caller, or NULL for one
  * created for the call.  ws: logra_influence_stream_ws_size(Q, chunk_rows,
  * D, tr_dtype, topk) bytes (two staging buffers and one chunk's scoring

@@ -367,8 +367,8 @@ size_t logra_influence_ws_size(int Q, int64_t N_chunk, int topk, int scores_give
 static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, int Q, const void *g_train,
                           int tr_dtype, int64_t ld_tr, int64_t N_chunk, int D, int64_t train_base,
                           float *scores, int64_t ld_s, int topk, float *topk_val, int64_t *topk_idx, int merge,
-                          const float *row_scale, const float *col_scale, void *ws, size_t ws_bytes,
-                          void *stream) {
+                          const float *row_scale, const float *col_scale, int64_t at, int64_t store_rows, void *ws,
+                          size_t ws_bytes, void *stream) {
     TRY(check_score_dtypes(te_dtype, tr_dtype));
     if (Q < 0 || N_chunk < 0 || D <= 0) return fail(LOGRA_ERR_INVALID_ARG, "need Q >= 0, N_chunk >= 0, D > 0");
     if (ld_te < D || ld_tr < D) return fail(LOGRA_ERR_INVALID_ARG, "ld_te and ld_tr must be >= D");
@@ -402,7 +402,6 @@ static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, i
     TRY(check_dev(g_train, "g_train", bf16 ? 16 : esize(tr_dtype)));
     if (row_scale) TRY(check_dev(row_scale, "row_scale", 4));
     if (col_scale) TRY(check_dev(col_scale, "col_scale", 4));
-    const logra::ScoreScale scale{row_scale, col_scale};
     const size_t need = logra_influence_ws_size(Q, N_chunk, topk, scores != nullptr);
     if (need) TRY(check_ws(ws, ws_bytes, need));
     char *wp = static_cast<char *>(ws);
@@ -416,10 +415,35 @@ static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, i
         wp += round256(sizeof(float) * static_cast<size_t>(Q) * static_cast<size_t>(N_chunk));
     }
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t pre = (bf16 && topk > 0) ? logra::topk_prefix_rows(N_chunk, topk) : 0;
+    int64_t pre = (bf16 && topk > 0) ? logra::topk_prefix_rows(N_chunk, topk) : 0;
+    // The order of each score's sum: that of one call over the store_rows rows
+    // of the store, which scores its first rows (its own prefix) and the others
+    // in two launches.  `cut` is the first row of this chunk among the others; a
+    // filtered launch never holds it: the prefix may reach up to it instead.
+    logra::ScoreOrder head = logra::kOneChain, tail = logra::kOneChain;
+    int64_t cut = 0;
+    if (bf16) {
+        const int64_t store_pre = topk > 0 ? logra::topk_prefix_rows(store_rows, topk) : 0;
+        head = tail = logra::score_order(Q, store_rows - store_pre, D);
+        if (store_pre > 0) head = logra::score_order(Q, store_pre, D);
+        if (head != tail && store_pre > at) cut = store_pre - at < N_chunk ? store_pre - at : N_chunk;
+        if (pre > 0 && cut > pre && cut < N_chunk) pre = cut;
+    }
+    // scores of the chunk's rows from .. to
+    auto score = [&](int64_t from, int64_t to, const logra::ScoreFilter *filt) {
+        hipError_t e = hipSuccess;
+        while (from < to && e == hipSuccess) {
+            const int64_t end = from < cut && cut < to ? cut : to;
+            const logra::ScoreScale part{row_scale, col_scale ? col_scale + from : nullptr};
+            e = logra::launch_scores(g_test_pre, te_dtype, ld_te, Q,
+                                     static_cast<const char *>(g_train) + static_cast<size_t>(from * ld_tr) * esize(tr_dtype),
+                                     tr_dtype, ld_tr, end - from, D, s_buf + from, ld, filt, part, from < cut ? head : tail, s);
+            from = end;
+        }
+        return e;
+    };
     if (pre == 0) {
-        hipError_t e = logra::launch_scores(g_test_pre, te_dtype, ld_te, Q, g_train, tr_dtype, ld_tr, N_chunk, D,
-                                            s_buf, ld, nullptr, scale, s);
+        hipError_t e = score(0, N_chunk, nullptr);
         if (e != hipSuccess) return hip_fail(e, "score launch");
         if (topk > 0) {
             e = logra::launch_topk(s_buf, ld, Q, N_chunk, train_base, topk, topk_val, topk_idx, merge != 0, s);
@@ -435,18 +459,14 @@ static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, i
     int *cnt = reinterpret_cast<int *>(wp + q4);
     float *cval = reinterpret_cast<float *>(wp + 2 * q4);
     int *cidx = reinterpret_cast<int *>(wp + 2 * q4 + round256(4 * static_cast<size_t>(Q) * logra::kCandCap));
-    hipError_t e = logra::launch_scores(g_test_pre, LOGRA_BF16, ld_te, Q, g_train, LOGRA_BF16, ld_tr, pre, D, s_buf,
-                                        ld, nullptr, scale, s);
+    hipError_t e = score(0, pre, nullptr);
     if (e != hipSuccess) return hip_fail(e, "score launch");
     e = logra::launch_topk(s_buf, ld, Q, pre, train_base, topk, topk_val, topk_idx, merge != 0, s);
     if (e != hipSuccess) return hip_fail(e, "top-k launch");
     e = logra::launch_topk_threshold(topk_val, topk_idx, Q, topk, thr, cnt, s);
     if (e != hipSuccess) return hip_fail(e, "top-k threshold launch");
     const logra::ScoreFilter filt{thr, cnt, cval, cidx, logra::kCandCap};
-    const void *tr_rest = static_cast<const uint16_t *>(g_train) + pre * ld_tr;
-    const logra::ScoreScale scale_rest{row_scale, col_scale ? col_scale + pre : nullptr};
-    e = logra::launch_scores(g_test_pre, LOGRA_BF16, ld_te, Q, tr_rest, LOGRA_BF16, ld_tr, N_chunk - pre, D,
-                             s_buf + pre, ld, &filt, scale_rest, s);
+    e = score(pre, N_chunk, &filt);
     if (e != hipSuccess) return hip_fail(e, "score launch");
     e = logra::launch_topk_filtered(s_buf + pre, ld, Q, N_chunk - pre, train_base + pre, topk, topk_val, topk_idx,
                                     cnt, cval, cidx, logra::kCandCap, s);
@@ -454,13 +474,13 @@ static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, i
     return ok();
 }
 
-
 int logra_influence_scores(const void *g_test_pre, int te_dtype, int64_t ld_te, int Q,
                            const void *g_train, int tr_dtype, int64_t ld_tr, int64_t N_chunk, int D,
                            int64_t train_base, float *scores, int64_t ld_s, int topk, float *topk_val,
                            int64_t *topk_idx, int merge, void *ws, size_t ws_bytes, void *stream) {
     return influence_impl(g_test_pre, te_dtype, ld_te, Q, g_train, tr_dtype, ld_tr, N_chunk, D, train_base,
-                          scores, ld_s, topk, topk_val, topk_idx, merge, nullptr, nullptr, ws, ws_bytes, stream);
+                          scores, ld_s, topk, topk_val, topk_idx, merge, nullptr, nullptr, 0, N_chunk, ws, ws_bytes,
+                          stream);
 }
 
 int logra_influence_scores_scaled(const void *g_test_pre, int te_dtype, int64_t ld_te, int Q,
@@ -469,9 +489,20 @@ int logra_influence_scores_scaled(const void *g_test_pre, int te_dtype, int64_t 
                                   float *scores, int64_t ld_s, int topk, float *topk_val, int64_t *topk_idx,
                                   int merge, void *ws, size_t ws_bytes, void *stream) {
     return influence_impl(g_test_pre, te_dtype, ld_te, Q, g_train, tr_dtype, ld_tr, N_chunk, D, train_base,
-                          scores, ld_s, topk, topk_val, topk_idx, merge, row_scale, col_scale, ws, ws_bytes,
-                          stream);
+                          scores, ld_s, topk, topk_val, topk_idx, merge, row_scale, col_scale, 0, N_chunk, ws,
+                          ws_bytes, stream);
 }
+
+}  // extern "C"
+
+int logra::influence_chunk(const void *g_test_pre, int te_dtype, int64_t ld_te, int Q, const void *g_train, int tr_dtype,
+                           int64_t ld_tr, int64_t N_chunk, int D, int64_t at, int64_t store_rows, int topk,
+                           float *topk_val, int64_t *topk_idx, int merge, void *ws, size_t ws_bytes, void *stream) {
+    return influence_impl(g_test_pre, te_dtype, ld_te, Q, g_train, tr_dtype, ld_tr, N_chunk, D, at, nullptr, 1, topk,
+                          topk_val, topk_idx, merge, nullptr, nullptr, at, store_rows, ws, ws_bytes, stream);
+}
+
+extern "C" {
 
 size_t logra_self_influence_ws_size(int D, int n_blocks) {
     if (D <= 0 || n_blocks <= 0) return 0;
@@ -581,8 +612,8 @@ int logra_influence_stream(const void *g_test_pre, int te_dtype, int64_t ld_te, 
             rc = hip_fail(e, "chunk copy");
             break;
         }
-        rc = logra_influence_scores(g_test_pre, te_dtype, ld_te, Q, buf[b], tr_dtype, D, rows, D, r0, nullptr, 1,
-                                    topk, topk_val, topk_idx, c > 0, iws, iws_bytes, stream);
+        rc = logra::influence_chunk(g_test_pre, te_dtype, ld_te, Q, buf[b], tr_dtype, D, rows, D, r0, N, topk,
+                                    topk_val, topk_idx, c > 0, iws, iws_bytes, stream);
         if (rc == LOGRA_OK && (e = hipEventRecord(freed[b], cs)) != hipSuccess) rc = hip_fail(e, "event record");
     }
     // synchronous: the buffers, events and (own) stream live until the last chunk is scored

@@ -128,11 +128,24 @@ struct ScoreScale {
     const float *row;
     const float *col;
 };
+// The order in which the products of a bf16 score are summed: in one chain
+// (256 x 256 tiles), or in four bands of columns that are added at the end
+// (every smaller tile).  A score's bits depend on the order alone.
+enum ScoreOrder { kOneChain, kFourBands };
+// The order of the faster tiles for Q x N scores of D columns.
+ScoreOrder score_order(int Q, int64_t N, int D);
 // te_dt / tr_dt: both kBF16 (bf16 MFMA), or each kF32 or kF64 (float64
-// accumulation, no filter).
+// accumulation in one order whatever the sizes: `order` is not read; no filter).
 hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const void *tr, int tr_dt,
                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s, const ScoreFilter *filt,
-                         const ScoreScale &scale, hipStream_t st);
+                         const ScoreScale &scale, ScoreOrder order, hipStream_t st);
+// logra_influence_scores without scales or a score output, for rows at .. at +
+// N_chunk of a store of store_rows rows that is scored chunk by chunk: every
+// score has the bits that one call over the whole store would give it, so that
+// the merged top-k is that call's whatever the chunks.
+int influence_chunk(const void *g_test_pre, int te_dtype, int64_t ld_te, int Q, const void *g_train, int tr_dtype,
+                    int64_t ld_tr, int64_t N_chunk, int D, int64_t at, int64_t store_rows, int topk, float *topk_val,
+                    int64_t *topk_idx, int merge, void *ws, size_t ws_bytes, void *stream);
 // Rows of a chunk scored and selected exactly before candidate filtering
 // starts (their running top-k sets the thresholds); 0 = no filtering.
 int64_t topk_prefix_rows(int64_t N, int k);

@@ -848,15 +848,17 @@ struct ScoreTile {
 constexpr ScoreTile kScoreTiles[] = {{256, 256, 30., 16.4}, {64, 64, 5., 4.7}, {32, 64, 4., 3.5},
                                      {16, 64, 4., 2.8},     {32, 32, 3., 2.4}, {16, 16, 3., 1.15}};
 
-int score_tile(int Q, int64_t N, int D) {
-    int best = 0;
+// The cheapest of the tiles first .. last.
+constexpr int kLastTile = static_cast<int>(sizeof kScoreTiles / sizeof kScoreTiles[0]) - 1;
+int score_tile(int Q, int64_t N, int D, int first, int last) {
+    int best = first;
     double cost = 0.;
-    for (int v = 0; v < static_cast<int>(sizeof kScoreTiles / sizeof kScoreTiles[0]); ++v) {
+    for (int v = first; v <= last; ++v) {
         const ScoreTile &t = kScoreTiles[v];
         const int64_t m_tiles = (Q + t.m - 1) / t.m, n_tiles = (N + t.n - 1) / t.n;
         const int64_t rounds = ((n_tiles + kXcd - 1) / kXcd * m_tiles + 31) / 32;
         const double c = static_cast<double>(rounds) * (t.fixed + t.per_k * D / 1024.);
-        if (v == 0 || c < cost) {
+        if (v == first || c < cost) {
             best = v;
             cost = c;
         }
@@ -865,12 +867,14 @@ int score_tile(int Q, int64_t N, int D) {
 }
 }  // namespace
 
+ScoreOrder score_order(int Q, int64_t N, int D) { return score_tile(Q, N, D, 0, kLastTile) == 0 ? kOneChain : kFourBands; }
+
 hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const void *tr, int tr_dt,
                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s, const ScoreFilter *filt,
-                         const ScoreScale &scale, hipStream_t st) {
+                         const ScoreScale &scale, ScoreOrder order, hipStream_t st) {
     if (Q == 0 || N == 0) return hipSuccess;
     if (te_dt == kBF16 && tr_dt == kBF16) {
-        const int tile = score_tile(Q, N, D);
+        const int tile = order == kOneChain ? 0 : score_tile(Q, N, D, 1, kLastTile);
         const int m_tiles = (Q + kScoreTiles[tile].m - 1) / kScoreTiles[tile].m;
         const int n_tiles = static_cast<int>((N + kScoreTiles[tile].n - 1) / kScoreTiles[tile].n);
         const int n_groups = (n_tiles + kXcd - 1) / kXcd;

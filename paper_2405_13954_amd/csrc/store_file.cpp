@@ -234,8 +234,8 @@ int logra_influence_stream_file(const void *g_test_pre, int te_dtype, int64_t ld
             rc = logra::hip_fail(e, "order the scoring after the copy");
             break;
         }
-        rc = logra_influence_scores(g_test_pre, te_dtype, ld_te, Q, dbuf[b], tr_dtype, D, rows, D, r0, nullptr, 1,
-                                    topk, topk_val, topk_idx, c > 0, iws, iws_bytes, stream);
+        rc = logra::influence_chunk(g_test_pre, te_dtype, ld_te, Q, dbuf[b], tr_dtype, D, rows, D, r0, N, topk,
+                                    topk_val, topk_idx, c > 0, iws, iws_bytes, stream);
         if (rc == LOGRA_OK && (e = hipEventRecord(freed[b], cs)) != hipSuccess) rc = logra::hip_fail(e, "event record");
     }
     {

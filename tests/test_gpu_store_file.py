@@ -118,6 +118,23 @@ def test_stream_file_equals_resident_from_disk(path):
     assert np.array_equal(ti2, ri) and np.array_equal(tv2, rv)
 
 
+def test_stream_file_equals_resident_in_both_orders(path):
+    """Sizes at which the whole store's call sums the first 4,096 rows' scores in four bands and the others' in one
+    chain, and a chunk on its own would do otherwise."""
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    say("[store file] real scores, 1,000 queries x 20,000 rows of 1,024 bf16, chunks of 3,000 and 9,000")
+    g = W.rng(92)
+    Q, N, D, k = 1000, 20_000, 1024, 30
+    te = W.normal(g, (Q, D), 1.0, "bf16")
+    tr = W.normal(g, (N, D), 1.0, "bf16")
+    tr.tofile(path)
+    rv, ri = _resident(te, tr, k)
+    for chunk in (3_000, 9_000):
+        tv, ti = _stream_file(path, te, N, D, P.BF16, k, chunk)
+        assert np.array_equal(ti, ri) and np.array_equal(tv, rv), chunk
+
+
 def test_stream_file_short_file_is_an_io_error(path):
     import torch
     import paper_2405_13954_amd as P

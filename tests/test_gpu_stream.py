@@ -2,8 +2,8 @@
 in chunks through two device staging buffers (Sec. 4.2: the reading of
 training gradients overlapped with the influence computation) must give the
 exact top-k of the whole store -- bit for bit the oracle's on integer scores,
-and bit for bit the device-resident call's on real-valued ones (every score
-is the same dot product in the same order wherever its row sits)."""
+and bit for bit the device-resident call's on real-valued ones (a row's dot
+products are summed in the order of that call whatever chunk the row is in)."""
 import numpy as np
 import pytest
 
@@ -94,3 +94,29 @@ def test_stream_single_chunk_empty_store_and_pageable_rejected():
     with pytest.raises(P.LograError) as ei:
         P.logra_influence_stream(dev(te), torch.from_numpy(tr), 8, tvd, tid, 100)   # pageable
     assert ei.value.status == P.ERR_INVALID_ARG and "pinned" in P.logra_last_error()
+
+
+@pytest.mark.parametrize("Q,N,D,k,chunks", [
+    (300, 40_000, 1024, 1000, (333, 3_000, 8_200, 9_000, 12_000, 39_999, 50_000)),   # 9,984 rows in bands, the others in one chain
+    (1000, 20_000, 1024, 30, (700, 9_000)),                                         # 4,096 in bands
+    (600, 40_000, 1024, 1000, (1_500, 8_200)),                                      # one chain, short chunks alone take bands
+    (40, 20_000, 520, 7, (100, 9_000))])                                            # bands
+def test_stream_equals_resident_in_every_order(Q, N, D, k, chunks):
+    """bf16 scores are summed in one chain or in four bands of columns, by the sizes of a launch; a streamed row takes
+    the order of the whole store's call.  Chunks that end before, across and after the first rows of the store that
+    the whole call scores on their own, with and without candidate lists of their own."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    say(f"[stream orders] Q={Q} N={N} D={D} k={k} chunks={chunks}")
+    gen = W.torch_generator(74, Q)
+    te = torch.randn((Q, D), generator=gen, device="cuda").bfloat16()
+    tr = torch.randn((N, D), generator=gen, device="cuda").bfloat16()
+    rv = torch.empty((Q, k), dtype=torch.float32, device="cuda")
+    ri = torch.empty((Q, k), dtype=torch.int64, device="cuda")
+    P.logra_influence_scores(te, tr, topk=k, topk_val=rv, topk_idx=ri)
+    store = tr.cpu().pin_memory()
+    for chunk in chunks:
+        tv, ti = torch.empty_like(rv), torch.empty_like(ri)
+        P.logra_influence_stream(te, store, k, tv, ti, chunk)
+        assert torch.equal(ti, ri) and torch.equal(tv, rv), chunk
