@@ -253,3 +253,50 @@ def test_scores_tile_shapes(Q, N, D, k, scaled):
         wv, wi = oracle.topk(f64(got[:, :N]), k)
         assert np.array_equal(host(ti), wi)
         assert np.array_equal(f64(host(tv)), wv)
+
+
+@pytest.mark.parametrize("Q,N,D", [(13, 30_000, 64), (20, 9_000, 64), (30, 30_000, 64), (50, 33_000, 64), (300, 66_000, 16)])
+def test_topk_candidates_of_tied_and_rising_scores(Q, N, D):
+    """Long chunks in tiles of 16 x 64, 32 x 32, 32 x 64, 64 x 64 and 256 x 256: rows whose scores all tie, rise along
+    the chunk (every later one is a candidate, and the list overflows), fall or are small integers.  The top-k is the
+    oracle's, and many candidates cost no more than a few times what few do (a row's candidates of a tile take their
+    places together)."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, f64, host, say
+    say(f"[top-k candidates] Q={Q} N={N} D={D}")
+    g = W.rng(49, Q, N, D)
+    k = 100
+    te = W.integer_array(g, (Q, D), -2, 2, "f32")
+    te[:, 0] = 0.0
+    te[0::4] = 0.0                                  # ties
+    te[1::4] = 0.0
+    te[1::4, 0] = 1.0                               # rising
+    te[2::4] = 0.0
+    te[2::4, 0] = -1.0                              # falling
+    tr = W.integer_array(g, (N, D), -2, 2, "f32")
+    tr[:, 0] = np.arange(N) // 512                  # exact in bf16
+    te, tr = W.f32_to_bf16_bits(te), W.f32_to_bf16_bits(tr)
+    wv, wi = oracle.topk(oracle.scores(te, tr), k)
+    tv = torch.empty((Q, k), dtype=torch.float32, device="cuda")
+    ti = torch.empty((Q, k), dtype=torch.int64, device="cuda")
+    ws = torch.empty(P.logra_influence_ws_size(Q, N, k, False), dtype=torch.uint8, device="cuda")
+    trd, ted = dev(tr), dev(te)
+
+    def best_ms(t):
+        ms = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            P.logra_influence_scores(t, trd, topk=k, topk_val=tv, topk_idx=ti, ws=ws)
+            b.record()
+            b.synchronize()
+            ms.append(a.elapsed_time(b))
+        return min(ms)
+
+    few = best_ms(torch.randn((Q, D), device="cuda").bfloat16() * (torch.arange(D, device="cuda") > 0))
+    many = best_ms(ted)
+    say(f"  few candidates {few:.3f} ms, many {many:.3f} ms")
+    assert np.array_equal(host(ti), wi)
+    assert np.array_equal(f64(host(tv)), wv)
+    assert many <= 15.0 * few   # 3 to 5 measured (an overflowing row is selected from all its scores); 78 to 190 one by one
