@@ -257,9 +257,9 @@ int logra_precondition_f64(const double *S, int D, int n_blocks, int64_t N, doub
  * candidates (up to 8192 per query), and the candidates are merged; a query
  * whose candidates overflow is selected from its full score row.  The result
  * is the same exact top-k in every case.
- * The order of a bf16 score's fp32 sum depends on Q, N_chunk and D (and, in a
- * long chunk, on whether the row is in the prefix), so a row scored within a
- * chunk of another length may differ in its last bits.
+ * The order of a score's sum depends on Q, N_chunk and D (and, in a long bf16
+ * chunk, on whether the row is in the prefix), so a row scored within a chunk
+ * of another length may differ by the rounding of its sum.
  * N_chunk < 2^31; for bf16, ld_te and ld_tr < 2^22.
  * Scores of NaN order unspecified.
  * ---------------------------------------------------------------------- */

@@ -420,15 +420,12 @@ static int influence_impl(const void *g_test_pre, int te_dtype, int64_t ld_te, i
     // of the store, which scores its first rows (its own prefix) and the others
     // in two launches.  `cut` is the first row of this chunk among the others; a
     // filtered launch never holds it: the prefix may reach up to it instead.
-    logra::ScoreOrder head = logra::kOneChain, tail = logra::kOneChain;
-    int64_t cut = 0;
-    if (bf16) {
-        const int64_t store_pre = topk > 0 ? logra::topk_prefix_rows(store_rows, topk) : 0;
-        head = tail = logra::score_order(Q, store_rows - store_pre, D);
-        if (store_pre > 0) head = logra::score_order(Q, store_pre, D);
-        if (head != tail && store_pre > at) cut = store_pre - at < N_chunk ? store_pre - at : N_chunk;
-        if (pre > 0 && cut > pre && cut < N_chunk) pre = cut;
-    }
+    const int64_t store_pre = (bf16 && topk > 0) ? logra::topk_prefix_rows(store_rows, topk) : 0;
+    const logra::ScoreOrder tail = logra::score_order(bf16, Q, store_rows - store_pre, D);
+    const logra::ScoreOrder head = store_pre > 0 ? logra::score_order(bf16, Q, store_pre, D) : tail;
+    const int64_t first_tail = head != tail && store_pre > at ? store_pre - at : 0;
+    const int64_t cut = first_tail < N_chunk ? first_tail : N_chunk;
+    if (pre > 0 && cut > pre && cut < N_chunk) pre = cut;
     // scores of the chunk's rows from .. to
     auto score = [&](int64_t from, int64_t to, const logra::ScoreFilter *filt) {
         hipError_t e = hipSuccess;

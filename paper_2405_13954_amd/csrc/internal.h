@@ -128,14 +128,15 @@ struct ScoreScale {
     const float *row;
     const float *col;
 };
-// The order in which the products of a bf16 score are summed: in one chain
-// (256 x 256 tiles), or in four bands of columns that are added at the end
-// (every smaller tile).  A score's bits depend on the order alone.
+// The order in which the products of a score are summed: in one chain (bf16:
+// 256 x 256 tiles; fp32 / fp64: k_scores_f64_chain), or in four bands of columns
+// that are added at the end (every other tile).  A score's bits depend on the
+// order alone.
 enum ScoreOrder { kOneChain, kFourBands };
 // The order of the faster tiles for Q x N scores of D columns.
-ScoreOrder score_order(int Q, int64_t N, int D);
+ScoreOrder score_order(bool bf16, int Q, int64_t N, int D);
 // te_dt / tr_dt: both kBF16 (bf16 MFMA), or each kF32 or kF64 (float64
-// accumulation in one order whatever the sizes: `order` is not read; no filter).
+// accumulation, no filter).
 hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const void *tr, int tr_dt,
                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s, const ScoreFilter *filt,
                          const ScoreScale &scale, ScoreOrder order, hipStream_t st);

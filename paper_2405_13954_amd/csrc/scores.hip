@@ -12,8 +12,8 @@
 // over the 8 XCDs), so the slab is fetched from HBM once into that XCD's L2.
 // Operands are copied straight from memory into an LDS ring with gfx950's
 // buffer_load ... lds (no register staging); the issue order of MFMAs,
-// copies and fragment reads is fixed by hand.  fp32 / fp64 operands take a
-// float64-accumulating tiled kernel.
+// copies and fragment reads is fixed by hand.  fp32 / fp64 operands take two
+// float64-accumulating kernels.
 //
 // Top-k: one workgroup per query row.  An exact radix select (four 8-bit
 // passes over order-preserving keys) finds the k-th largest score; when more
@@ -472,10 +472,8 @@ __global__ __launch_bounds__(GT, 1) void k_scores_small(const bf16_bits *__restr
 // ahead (lane (r, q) reads columns 2 q, 2 q + 1, 2 q + 8, 2 q + 9 of a unit of
 // row r, for the four MFMAs of the unit, of both operands), and the four
 // partial tiles are added in fixed order through LDS.  Scales (normalised
-// scores) multiply in float64 before the rounding.  F: the largest tile that
-// still gives every CU a workgroup.  Bound by latency at the sizes of fp32
-// workloads: 8 x 32 rows of 1,024 columns 14 us; 130 in a 64 x 64 tile of scalar
-// FMAs.
+// scores) multiply in float64 before the rounding.  Bound by latency at the sizes
+// of fp32 workloads: 8 x 32 rows of 1,024 columns 22 us; 116 in k_scores_f64_chain.
 template <int F, typename TA, typename TB>
 __global__ __launch_bounds__(256) void k_scores_f64acc(const TA *te, int64_t ld_te, int Q, const TB *tr,
                                                        int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s,
@@ -554,6 +552,66 @@ __global__ __launch_bounds__(256) void k_scores_f64acc(const TA *te, int64_t ld_
         if (scale.row) val *= static_cast<double>(scale.row[q0 + m]);
         if (scale.col) val *= static_cast<double>(scale.col[j]);
         s[static_cast<int64_t>(q0 + m) * ld_s + j] = static_cast<float>(val);
+    }
+}
+
+// The same scores in one chain of FMAs over the columns, for many scores of few
+// columns: one 64 x 64 output tile per workgroup, 16-column slabs of both
+// operands staged through LDS as float64 (coalesced row reads, transposed
+// stores), 4 x 4 outputs a thread.  Bound by the fp64 FMAs and their LDS reads,
+// with nothing to fold at the end.  Measured against the bands in 64 x 64 tiles
+// (fp32 operands): 1,024 x 16,384 scores of 16 columns 36 us against 113, of 64
+// 78 against 154, of 256 266 against 388, of 768 787 against 842, of 1,024 1,050
+// against 1,057 (1,024 x 4,096: 287 against 272).
+constexpr int kChainTile = 64, kChainCols = 16;
+template <typename TA, typename TB>
+__global__ __launch_bounds__(256) void k_scores_f64_chain(const TA *te, int64_t ld_te, int Q, const TB *tr,
+                                                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s,
+                                                          ScoreScale scale) {
+    __shared__ double As[kChainCols][kChainTile + 1];   // [column][query]
+    __shared__ double Bs[kChainCols][kChainTile + 1];   // [column][train row]
+    const int q0 = blockIdx.y * kChainTile;
+    const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kChainTile;
+    const int tid = threadIdx.x, ta = tid >> 4, tb = tid & 15;
+    double acc[4][4] = {};
+    for (int k0 = 0; k0 < D; k0 += kChainCols) {
+#pragma unroll
+        for (int u = 0; u < kChainTile * kChainCols / 256; ++u) {
+            const int e = tid + 256 * u, r = e / kChainCols, c = e % kChainCols, d = k0 + c;
+            const int q = q0 + r;
+            const int64_t j = j0 + r;
+            As[c][r] = (q < Q && d < D) ? load_in_d<TA>(te + static_cast<int64_t>(q) * ld_te + d) : 0.0;
+            Bs[c][r] = (j < N && d < D) ? load_in_d<TB>(tr + j * ld_tr + d) : 0.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kChainCols; ++c) {
+            double x[4], y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                x[u] = As[c][4 * ta + u];
+                y[u] = Bs[c][tb + 16 * u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[u][v] = fma(x[u], y[v], acc[u][v]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int q = q0 + 4 * ta + u;
+        if (q >= Q) continue;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t j = j0 + tb + 16 * v;   // consecutive threads: consecutive columns
+            if (j >= N) continue;
+            double val = acc[u][v];
+            if (scale.row) val *= static_cast<double>(scale.row[q]);
+            if (scale.col) val *= static_cast<double>(scale.col[j]);
+            s[static_cast<int64_t>(q) * ld_s + j] = static_cast<float>(val);
+        }
     }
 }
 
@@ -887,9 +945,18 @@ int score_tile(int Q, int64_t N, int D, int first, int last) {
     }
     return best;
 }
+
+int64_t square_tiles(int Q, int64_t N, int64_t edge) { return (N + edge - 1) / edge * ((Q + edge - 1) / edge); }
 }  // namespace
 
-ScoreOrder score_order(int Q, int64_t N, int D) { return score_tile(Q, N, D, 0, kLastTile) == 0 ? kOneChain : kFourBands; }
+// fp32 / fp64: one chain where two 64 x 64 tiles or more fall to every CU and
+// the rows are short (times at k_scores_f64_chain: the bands win from about
+// 1,000 columns on), but not of 32 rows or fewer, which fill half of such a
+// tile (16 x 60,000 scores of 256 columns: 80 us, 57 in 32 x 32 tiles of bands).
+ScoreOrder score_order(bool bf16, int Q, int64_t N, int D) {
+    if (bf16) return score_tile(Q, N, D, 0, kLastTile) == 0 ? kOneChain : kFourBands;
+    return Q > 32 && N > 32 && D <= 768 && square_tiles(Q, N, 64) >= 512 ? kOneChain : kFourBands;
+}
 
 hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const void *tr, int tr_dt,
                          int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s, const ScoreFilter *filt,
@@ -918,8 +985,11 @@ hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const 
         }
     }
     if (filt || te_dt == kBF16 || tr_dt == kBF16) return hipErrorInvalidValue;   // bf16 pairs only with bf16
-    auto tiles = [&](int64_t t) { return (N + t - 1) / t * ((Q + t - 1) / t); };
-    const int f = tiles(64) >= 256 ? 4 : tiles(32) >= 256 ? 2 : 1;
+    // bands: the largest tile that gives every CU a workgroup; 64 x 64 neither for 32 rows or fewer (above)
+    // nor for rows so short that its fold outlasts its products (64 x 16,384 scores of 16 columns 17 us, 14.5
+    // in 32 x 32 tiles; of 96 the same; of 256 35 against 41)
+    const bool wide = square_tiles(Q, N, 64) >= 256 && Q > 32 && N > 32 && D > 96;
+    const int f = order == kOneChain || wide ? 4 : square_tiles(Q, N, 32) >= 256 ? 2 : 1;
     const dim3 grid(static_cast<unsigned>((N + 16 * f - 1) / (16 * f)), static_cast<unsigned>((Q + 16 * f - 1) / (16 * f)));
     auto go = [&](auto a, auto b) {
         using TA = decltype(a);
@@ -929,6 +999,7 @@ hipError_t launch_scores(const void *te, int te_dt, int64_t ld_te, int Q, const 
                                static_cast<const TB *>(tr), ld_tr, N, D, s, ld_s, scale);
             return hipGetLastError();
         };
+        if (order == kOneChain) return run(k_scores_f64_chain<TA, TB>);   // 64 x 64 tiles
         return f == 4 ? run(k_scores_f64acc<4, TA, TB>) : f == 2 ? run(k_scores_f64acc<2, TA, TB>) : run(k_scores_f64acc<1, TA, TB>);
     };
     if (te_dt == kF64) return tr_dt == kF64 ? go(double{}, double{}) : go(double{}, float{});

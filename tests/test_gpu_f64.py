@@ -122,10 +122,12 @@ def test_scores_f64_accumulation(te_dt, tr_dt, Q, N, D):
 
 @pytest.mark.parametrize("te_dt,tr_dt,Q,N,D", [("f64", "f32", 1, 1, 1), ("f32", "f32", 15, 17, 15), ("f64", "f64", 17, 300, 17),
                                                ("f32", "f64", 33, 9000, 50), ("f64", "f32", 130, 33, 257),
-                                               ("f32", "f32", 200, 5000, 40)])
+                                               ("f32", "f32", 200, 5000, 40), ("f64", "f32", 33, 32800, 17),
+                                               ("f32", "f64", 65, 16400, 50), ("f64", "f64", 100, 16500, 1),
+                                               ("f32", "f32", 32, 33000, 24), ("f32", "f32", 40, 9000, 97)])
 def test_scores_f64_tiles(te_dt, tr_dt, Q, N, D):
-    """The 16, 32 and 64 wide tiles of the float64 scores with remainders in rows and columns, strided operands, and
-    columns that the four bands do not share evenly: each score within half an fp32 ulp of the exact one plus the
+    """The 16, 32 and 64 wide tiles of the float64 scores in four bands and the 64 wide ones in one chain, with
+    remainders in rows and columns, strided operands, and columns that the bands do not share evenly: each score within half an fp32 ulp of the exact one plus the
     float64 sum's own rounding."""
     import torch
     import paper_2405_13954_amd as P

@@ -120,3 +120,32 @@ def test_stream_equals_resident_in_every_order(Q, N, D, k, chunks):
         tv, ti = torch.empty_like(rv), torch.empty_like(ri)
         P.logra_influence_stream(te, store, k, tv, ti, chunk)
         assert torch.equal(ti, ri) and torch.equal(tv, rv), chunk
+
+
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+@pytest.mark.parametrize("Q,N,D,chunks", [(80, 20_000, 33, (300, 4_000, 19_999)), (20, 20_000, 33, (300, 9_000))])
+def test_stream_f64_sums_equal_resident_in_both_orders(dt, Q, N, D, chunks):
+    """float64 sums whose large terms cancel, so that the order of the sum shows in the score: a streamed row takes the
+    whole store's order (one chain for 80 queries, in which short chunks alone would take bands; bands for 20)."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    say(f"[stream f64 orders] {dt} Q={Q} N={N} D={D} chunks={chunks}")
+    gen = W.torch_generator(75, Q)
+    t = torch.float32 if dt == "f32" else torch.float64
+    h = D // 2
+    te = torch.randn((Q, D), generator=gen, device="cuda") * 1e4
+    tr = torch.randn((N, D), generator=gen, device="cuda") * 1e4
+    te[:, h:2 * h] = te[:, :h]
+    tr[:, h:2 * h] = -tr[:, :h]
+    te[:, -1], tr[:, -1] = 1e-4, torch.randn(N, generator=gen, device="cuda") * 1e-4
+    te, tr = te.to(t), tr.to(t)
+    k = 50
+    rv = torch.empty((Q, k), dtype=torch.float32, device="cuda")
+    ri = torch.empty((Q, k), dtype=torch.int64, device="cuda")
+    P.logra_influence_scores(te, tr, topk=k, topk_val=rv, topk_idx=ri)
+    store = tr.cpu().pin_memory()
+    for chunk in chunks:
+        tv, ti = torch.empty_like(rv), torch.empty_like(ri)
+        P.logra_influence_stream(te, store, k, tv, ti, chunk)
+        assert torch.equal(ti, ri) and torch.equal(tv, rv), chunk
