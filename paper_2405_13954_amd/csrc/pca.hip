@@ -139,6 +139,17 @@ inline int tile_slots(int nt) {
     return (groups + 7) / 8 * 8 * kGR * kGC;
 }
 
+// Tiles that fall to each XCD in that order.
+inline void xcd_tiles(int nt, int64_t (&tiles)[8]) {
+    for (int64_t &t : tiles) t = 0;
+    const int ngr = (nt + kGR - 1) / kGR, ngc = (nt + kGC - 1) / kGC;
+    int g = 0;
+    for (int gr = 0; gr < ngr; ++gr)
+        for (int gc = gr / 2; gc < ngc; ++gc, ++g)
+            for (int r = gr * kGR; r < std::min(nt, (gr + 1) * kGR); ++r)
+                tiles[g & 7] += std::max(0, std::min(nt, (gc + 1) * kGC) - std::max(r, gc * kGC));
+}
+
 // Slabs of B examples of T tokens (spe = ceil(T / 32) per example): the
 // non-empty ones in order, with bit r of bits[] set iff token 32 s + r of the
 // example exists and is unmasked.  One workgroup, block-wide prefix counts.
@@ -437,9 +448,14 @@ __device__ __forceinline__ void act_cov_tile(const bf16_bits *__restrict__ a, in
 // within one whatever the factors' sizes.  Measured: the eight factors of a
 // GPT-2-small block over 8,000 tokens (231 tiles) 325 us, the eleven of a
 // Llama3-8B block 5.77 ms; 1,129 us and 6.70 ms with whole groups dealt from
-// XCD 0 on for each factor, which put all tiles of the small ones there.  One
-// factor alone of at least 256 tiles (`whole_groups`) keeps that order: 1.79 ms
-// at n = 14,336 against 1.84-1.91.
+// XCD 0 on for each factor, which put all tiles of the small ones there.
+// A first factor of at least 256 tiles, alone or with at most 64 tiles beside it,
+// keeps its groups whole where that costs no round more (its XCDs' shares are
+// uneven); the others' tiles then fill up the XCDs with the smallest shares.
+// 8,192 tokens, whole and filled against the list: n = 14,336 1.71 ms and 1.82, with
+// one of 1,024 beside it 1.69 and 1.81, 5,800 and 768 0.48 and 0.54; 11,008 alone
+// takes five rounds whole, 1.16 ms, and four as a list, 1.10; 14,336 and 4,096 (136
+// tiles) 1.90 and 1.87.
 struct ActCovFactor {
     const bf16_bits *a;
     float *C;
@@ -448,7 +464,8 @@ struct ActCovFactor {
 struct ActCovArgs {
     ActCovFactor f[kMaxActCovGroup];
     int count;
-    bool whole_groups;
+    int whole;     // workgroups of factor 0 in whole groups, or 0; the list starts behind them with factor 1
+    int fill[9];   // whole > 0: XCD x takes the list's tiles fill[x] .. fill[x + 1]
 };
 
 __host__ __device__ inline int act_cov_chunk(int tiles) { return tiles < 256 ? (tiles + 7) / 8 : 32; }
@@ -459,13 +476,21 @@ __global__ __launch_bounds__(256, 1) void k_act_cov_dma(ActCovArgs g, int T, int
                                                         const int *__restrict__ n_slabs) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[kCLds];
     int f = 0, ti, tj;
-    if (g.whole_groups) {
+    const int bid = static_cast<int>(blockIdx.x) - g.whole;
+    if (bid < 0) {
         if (!tile_of_slot(blockIdx.x, g.f[0].nt, ti, tj)) return;
     } else {
-        const int all = g.f[g.count - 1].tile_end, chunk = act_cov_chunk(all);
-        const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
-        const int n = (i / chunk * 8 + x) * chunk + i % chunk;
-        if (n >= all) return;
+        const int x = bid & 7, i = bid >> 3;   // g.whole is a multiple of 8
+        int n, end;
+        if (g.whole > 0) {
+            n = g.f[0].tile_end + g.fill[x] + i;
+            end = g.f[0].tile_end + g.fill[x + 1];
+        } else {
+            end = g.f[g.count - 1].tile_end;
+            const int chunk = act_cov_chunk(end);
+            n = (i / chunk * 8 + x) * chunk + i % chunk;
+        }
+        if (n >= end) return;
         while (n >= g.f[f].tile_end) ++f;
         tile_of(n - (f > 0 ? g.f[f - 1].tile_end : 0), g.f[f].nt, ti, tj);
     }
@@ -1662,9 +1687,25 @@ hipError_t launch_act_cov_group(const void *const *a, float *const *C, const int
             if (tiles > INT32_MAX - 256) return hipErrorInvalidValue;
             g.f[i] = {static_cast<const bf16_bits *>(a[f]), C[f], n[f], static_cast<int>(nt), static_cast<int>(tiles)};
         }
-        g.whole_groups = count == 1 && tiles >= 256;
-        const int64_t chunk = act_cov_chunk(static_cast<int>(tiles)), chunks = (tiles + chunk - 1) / chunk;
-        const int64_t grid = g.whole_groups ? tile_slots(g.f[0].nt) : (chunks + 7) / 8 * 8 * chunk;
+        const int64_t chunk = act_cov_chunk(static_cast<int>(tiles)), turns = ((tiles + chunk - 1) / chunk + 7) / 8;
+        int64_t grid = 8 * turns * chunk;
+        g.whole = 0;
+        const int64_t others = tiles - g.f[0].tile_end;
+        if (g.f[0].tile_end >= 256 && others <= 64) {
+            int64_t share[8], quota[8] = {};
+            xcd_tiles(g.f[0].nt, share);
+            for (int64_t t = 0; t < others; ++t) {   // each to the XCD that has least
+                const int64_t x = std::min_element(share, share + 8) - share;
+                ++share[x];
+                ++quota[x];
+            }
+            if ((*std::max_element(share, share + 8) + 31) / 32 <= (turns * chunk + 31) / 32) {
+                g.whole = tile_slots(g.f[0].nt);
+                g.fill[0] = 0;
+                for (int x = 0; x < 8; ++x) g.fill[x + 1] = g.fill[x] + static_cast<int>(quota[x]);
+                grid = g.whole + 8 * *std::max_element(quota, quota + 8);
+            }
+        }
         hipLaunchKernelGGL(k_act_cov_dma, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, g, T, spe, list, bits,
                            n_slabs);
     } else {

@@ -267,10 +267,11 @@ def test_pca_from_masked_activations_end_to_end():
     assert np.max(np.abs(ev - wev) / wev) <= 1e-4
 
 
-@pytest.mark.parametrize("ns", [[5800, 264, 2056], [2056, 2048, 1032, 776, 768, 520], [5640]])
+@pytest.mark.parametrize("ns", [[5800, 264, 2056], [2056, 2048, 1032, 776, 768, 520], [5640], [5640, 8], [6920],
+                                [5800, 2304, 40], [5800, 2304, 2304], [264, 5896, 1032]])
 def test_act_cov_tile_orders(ns):
-    """The three orders in which a launch's tiles go to the XCDs: chunks of 32 of a list of several factors (more than
-    256 tiles), eighths of a shorter one, and whole groups of one long factor.  Small integers, so every entry is
+    """The orders in which a launch's tiles go to the XCDs: chunks of 32 of a list (more than 256 tiles), eighths of a
+    shorter one, and whole groups of one long factor, alone or with few tiles of others beside them.  Small integers, so every entry is
     exact; the list of a group and the groups of a single call must give the same C."""
     import torch
     import paper_2405_13954_amd as P
