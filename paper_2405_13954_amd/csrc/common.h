@@ -139,10 +139,11 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
 }
 
 // 1 / sqrt(x) to about an ulp: the hardware estimate (relative error below
-// 2^-20) and one third-order step.
+// 2^-20) and one third-order step, whose residual h is a NaN for x = inf (the
+// maximum drops it: 1 / sqrt(inf) is 0).
 __device__ __forceinline__ double rsqrt_d(double x) {
     const double y = __builtin_amdgcn_rsq(x);
-    const double h = fma(-x * y, y, 1.0);
+    const double h = __builtin_fmax(fma(-x * y, y, 1.0), -1.0);
     return fma(y * h, fma(h, 0.375, 0.5), y);
 }
 

@@ -273,3 +273,24 @@ def test_precondition_not_pd_pivot(D, at):
         P.logra_precondition_blocks(dev(S), 1, 0.0, dev(np.ones((2, 3 * D), np.float32)), out)
     assert ei.value.status == P.ERR_NOT_PD
     assert f"block 1: pivot {at} " in P.logra_last_error()
+
+
+@pytest.mark.parametrize("D", [1, 16, 40, 256, 300, 600])
+def test_precondition_infinite_damping(D):
+    """lambda = inf, from an infinite damping ratio or an infinite entry on the diagonal: every solution is zero, as
+    the oracle's, and no pivot is reported (inf is positive)."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import dev, host, say
+    say(f"[precondition inf] D={D}")
+    S = W.spd_matrix(66, D, min(D, 40), scale=4.0)
+    Sinf = S.copy()
+    Sinf[D // 2, D // 2] = np.inf
+    g = W.normal(W.rng(67, D), (5, D), 1.0, "f32")
+    for M, damp in ((S, np.inf), (Sinf, 0.1)):
+        want, lam = oracle.precondition(M.astype(np.float64), 4, damp, g)
+        assert lam == np.inf and not want.any()
+        for f, t in ((P.logra_precondition, torch.float32), (P.logra_precondition_f64, torch.float64)):
+            out = torch.full((5, D), float("nan"), dtype=t, device="cuda")
+            f(dev(M.astype(np.float32 if t == torch.float32 else np.float64)), 4, damp, dev(g), out)
+            assert not host(out).any()
