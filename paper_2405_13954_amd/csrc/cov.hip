@@ -120,10 +120,11 @@ __global__ __launch_bounds__(256) void k_cov_bf16(const bf16_bits *g, int64_t ld
 
     // staging: thread -> (example r = tid / 8, 8 columns c8 = 8 * (tid % 8))
     const int sr = tid >> 3, sc = (tid & 7) * 8;
-    for (int b0 = 0; b0 < B; b0 += BK) {
-        const int b = b0 + sr;
+    static_assert(uint32_t{INT32_MAX} + BK > INT32_MAX, "a step past the largest B does not wrap");
+    for (uint32_t b0 = 0; b0 < static_cast<uint32_t>(B); b0 += BK) {
+        const uint32_t b = b0 + sr;
         u32x4 vi = {0u, 0u, 0u, 0u}, vj = {0u, 0u, 0u, 0u};
-        if (b < B) {
+        if (b < static_cast<uint32_t>(B)) {
             const bf16_bits *rowp = gb + static_cast<int64_t>(b) * ld;
             if (I + sc < D) vi = ld128(rowp + I + sc);
             if (!diag && J + sc < D) vj = ld128(rowp + J + sc);
@@ -410,17 +411,19 @@ __global__ __launch_bounds__(256) void k_cov_f64(const TG *g, int64_t ld, int B,
     const TG *gb = g + static_cast<size_t>(blk) * D;
     const int ia = min(I + c, D - 1), ja = min(J + c, D - 1);   // past D: any column, not stored
     f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int b0 = 0; b0 < B; b0 += 32) {
+    const uint32_t rows = B;
+    static_assert(uint32_t{INT32_MAX} + 32 > INT32_MAX, "a step past the largest B does not wrap");
+    for (uint32_t b0 = 0; b0 < rows; b0 += 32) {
         TG x[8], y[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const TG *row = gb + static_cast<int64_t>(min(b0 + 4 * s + q, B - 1)) * ld;
+            const TG *row = gb + static_cast<int64_t>(min(b0 + 4 * s + q, rows - 1)) * ld;
             x[s] = row[ia];
             y[s] = row[ja];
         }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {   // rows past B count as zero on both sides (they may not be finite)
-            const bool in = b0 + 4 * s + q < B;
+            const bool in = b0 + 4 * s + q < rows;
             acc = mfma16_f64(in ? static_cast<double>(x[s]) : 0.0, in ? static_cast<double>(y[s]) : 0.0, acc);
         }
     }
