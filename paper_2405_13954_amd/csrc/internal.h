@@ -27,6 +27,7 @@ constexpr int kMaxGroup = 48;   // layers per grouped projection launch
 constexpr int kMaxK = 128;
 constexpr int kMaxTopk = 1024;
 constexpr int kMaxPrecondD = 8192;
+constexpr int64_t kMaxGridThreads = int64_t{1} << 32;   // a launch has fewer threads than this in x
 
 // Workspace regions are carved at 256-byte boundaries.
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }

@@ -928,22 +928,24 @@ struct ScoreTile {
 constexpr ScoreTile kScoreTiles[] = {{256, 256, 30., 16.4}, {64, 64, 5., 4.7}, {32, 64, 4., 3.5},
                                      {16, 64, 4., 2.8},     {32, 32, 3., 2.4}, {16, 16, 3., 1.15}};
 
-// The cheapest of the tiles first .. last.
+// The cheapest of the tiles first .. last whose grid can be launched (small
+// tiles of very many rows cannot), or `first`.
 constexpr int kLastTile = static_cast<int>(sizeof kScoreTiles / sizeof kScoreTiles[0]) - 1;
 int score_tile(int Q, int64_t N, int D, int first, int last) {
-    int best = first;
+    int best = -1;
     double cost = 0.;
     for (int v = first; v <= last; ++v) {
         const ScoreTile &t = kScoreTiles[v];
         const int64_t m_tiles = (Q + t.m - 1) / t.m, n_tiles = (N + t.n - 1) / t.n;
-        const int64_t rounds = ((n_tiles + kXcd - 1) / kXcd * m_tiles + 31) / 32;
+        const int64_t per_xcd = (n_tiles + kXcd - 1) / kXcd * m_tiles, rounds = (per_xcd + 31) / 32;
+        if (per_xcd * kXcd * GT >= kMaxGridThreads) continue;
         const double c = static_cast<double>(rounds) * (t.fixed + t.per_k * D / 1024.);
-        if (v == first || c < cost) {
+        if (best < 0 || c < cost) {
             best = v;
             cost = c;
         }
     }
-    return best;
+    return best < 0 ? first : best;
 }
 
 int64_t square_tiles(int Q, int64_t N, int64_t edge) { return (N + edge - 1) / edge * ((Q + edge - 1) / edge); }

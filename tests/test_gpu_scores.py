@@ -300,3 +300,22 @@ def test_topk_candidates_of_tied_and_rising_scores(Q, N, D):
     assert np.array_equal(host(ti), wi)
     assert np.array_equal(f64(host(tv)), wv)
     assert many <= 15.0 * few   # 3 to 5 measured (an overflowing row is selected from all its scores); 78 to 190 one by one
+
+
+def test_scores_rows_beyond_the_small_tiles_grid():
+    """1.1e9 rows of eight columns against one query: in tiles of 64 rows that is more threads than a launch may have.
+    Integer rows, so every score is exact."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    N, D = 1_100_000_000, 8
+    say(f"[scores] 1 x {N} x {D}")
+    tr = torch.empty((N, D), dtype=torch.bfloat16, device="cuda")
+    step = 1 << 27
+    for r in range(0, N, step):
+        v = torch.arange(r, min(N, r + step), device="cuda", dtype=torch.int32) % 5 - 2
+        tr[r:r + step] = v.to(torch.bfloat16)[:, None]
+    s = torch.full((1, N), float("nan"), dtype=torch.float32, device="cuda")
+    P.logra_influence_scores(torch.ones((1, D), dtype=torch.bfloat16, device="cuda"), tr, s)
+    for r in range(0, N, step):
+        assert torch.equal(s[0, r:r + step], 8.0 * tr[r:r + step, 3].float())
