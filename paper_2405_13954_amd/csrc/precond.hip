@@ -378,6 +378,7 @@ struct SolveArgs {
     int src;               // where the right-hand sides come from
     int fwd, bwd;          // apply W, then W^T
     int to_y;              // write the result to Y
+    int wg0;               // number of the launch's first workgroup
 };
 
 template <int NBK, int NC>
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(512, 4) void k_solve(SolveArgs p) {
     constexpr int kCols = NC / kHalves;
     constexpr int kBat = NBK == 4 ? 2 : 4;
     __shared__ __attribute__((aligned(16))) double R[NBK * FB * kLd];
-    const int blk = blockIdx.y, q0 = blockIdx.x * 16 * NC, tid = threadIdx.x, lane = tid & 63;
+    const int blk = blockIdx.y, q0 = (p.wg0 + static_cast<int>(blockIdx.x)) * 16 * NC, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kg = lane >> 4;
     const int D = p.D, w = D - p.c0 < NBK * FB ? D - p.c0 : NBK * FB, nblk = (w + FB - 1) / FB;
@@ -973,16 +974,22 @@ __global__ __launch_bounds__(256) void k_copy_rows(const TIn *src, int64_t ld_in
         store_out_d<TOut>(dst + static_cast<int64_t>(r) * ld_out + c, load_in_d<TIn>(src + static_cast<int64_t>(r) * ld_in + c));
 }
 
-// One k_solve launch over the first `cols` right-hand sides, 32 of them per
-// workgroup (two workgroups share a CU), or 16 where that would leave CUs idle.
-hipError_t launch_solve_block(const SolveArgs &p, int cols, int n_blocks, hipStream_t s) {
+// k_solve over the first `cols` right-hand sides, 32 of them per workgroup (two
+// workgroups share a CU), or 16 where that would leave CUs idle; one launch, but
+// for more workgroups than a launch takes.
+hipError_t launch_solve_block(SolveArgs p, int cols, int n_blocks, hipStream_t s) {
     auto wgs = [&](int nc) { return (cols + 16 * nc - 1) / (16 * nc) * static_cast<int64_t>(n_blocks); };
     const int nc = wgs(2) >= 256 ? 2 : 1;
-    const dim3 grid(static_cast<unsigned>((cols + 16 * nc - 1) / (16 * nc)), static_cast<unsigned>(n_blocks));
+    const int all = (cols + 16 * nc - 1) / (16 * nc), most = static_cast<int>(kMaxGridThreads / 512 - 1);
     const int w = p.D - p.c0 < PB ? p.D - p.c0 : PB;
     auto go = [&](auto k) {
-        hipLaunchKernelGGL(k, grid, dim3(512), 0, s, p);
-        return hipGetLastError();
+        hipError_t e = hipSuccess;
+        for (p.wg0 = 0; p.wg0 < all && e == hipSuccess; p.wg0 += most) {
+            const dim3 grid(static_cast<unsigned>(min(most, all - p.wg0)), static_cast<unsigned>(n_blocks));
+            hipLaunchKernelGGL(k, grid, dim3(512), 0, s, p);
+            e = hipGetLastError();
+        }
+        return e;
     };
     if (w <= 64) return nc == 2 ? go(k_solve<4, 2>) : go(k_solve<4, 1>);
     if (w <= 128) return nc == 2 ? go(k_solve<8, 2>) : go(k_solve<8, 1>);
@@ -1066,7 +1073,7 @@ hipError_t launch_forward(const WsLayout &w, int D, int n_blocks, const void *g,
     for (int c0 = 0; c0 < D && e == hipSuccess; c0 += PB) {
         const int from = src == kFromG && c0 > 0 ? static_cast<int>(kFromY) : src;
         const int cols = src == kFromIdent && c0 + PB < Qp ? c0 + PB : Qp;
-        e = launch_solve_block(SolveArgs{w.A, w.Y, g, nullptr, ld_in, 0, D, c0, Q, Qp, in_dt, kF32, from, 1, 0, 1}, cols,
+        e = launch_solve_block(SolveArgs{w.A, w.Y, g, nullptr, ld_in, 0, D, c0, Q, Qp, in_dt, kF32, from, 1, 0, 1, 0}, cols,
                                n_blocks, s);
         const int rest = D - c0 - PB;
         if (rest <= 0 || e != hipSuccess) continue;
@@ -1143,11 +1150,11 @@ hipError_t launch_precondition(const void *S, bool s_f64, int D, int n_blocks, i
     const int Qp = padded_q(Q);
     if (D <= PB)
         return launch_solve_block(SolveArgs{w.A, nullptr, g_test, g_out, ld_in, ld_out, D, 0, Q, Qp, in_dt, out_dt, kFromG,
-                                            1, 1, 0},
+                                            1, 1, 0, 0},
                                   Q, n_blocks, s);
     e = launch_forward(w, D, n_blocks, g_test, in_dt, ld_in, Q, kFromG, s);
     for (int c0 = (D - 1) / PB * PB; c0 >= 0 && e == hipSuccess; c0 -= PB) {
-        e = launch_solve_block(SolveArgs{w.A, w.Y, nullptr, g_out, 0, ld_out, D, c0, Q, Qp, kF32, out_dt, kFromY, 0, 1, 1},
+        e = launch_solve_block(SolveArgs{w.A, w.Y, nullptr, g_out, 0, ld_out, D, c0, Q, Qp, kF32, out_dt, kFromY, 0, 1, 1, 0},
                                Qp, n_blocks, s);
         if (c0 == 0 || e != hipSuccess) continue;
         e = launch_solve_gemm<kBackward>(GemmArgs{w.A, w.Y, nullptr, 0, D, c0, Q, Qp, kF32, kFromY}, c0, Qp, n_blocks, s);

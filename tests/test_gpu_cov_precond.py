@@ -294,3 +294,17 @@ def test_precondition_infinite_damping(D):
             out = torch.full((5, D), float("nan"), dtype=t, device="cuda")
             f(dev(M.astype(np.float32 if t == torch.float32 else np.float64)), 4, damp, dev(g), out)
             assert not host(out).any()
+
+
+def test_precondition_more_right_hand_sides_than_one_grid():
+    """3e8 gradients of one value: more workgroups of 32 than one launch takes."""
+    import torch
+    import paper_2405_13954_amd as P
+    from gpu_util import say
+    Q = 300_000_000
+    say(f"[precondition] D=1, {Q} right-hand sides")
+    S = torch.tensor([[6.0]], device="cuda")
+    g = (torch.arange(Q, device="cuda", dtype=torch.int32) % 1000).to(torch.float32)[:, None]
+    out = torch.full((Q, 1), float("nan"), dtype=torch.float32, device="cuda")
+    P.logra_precondition(S, 2, 1.0, g, out)         # C = 3, lambda = 3
+    assert (out - g / 6.0).abs().max().item() <= 1000 / 6.0 * 2.0 ** -23
