@@ -399,11 +399,11 @@ __global__ __launch_bounds__(256) void k_cov_f32(const float *g, int64_t ld, int
 // scalar FMAs per workgroup.
 constexpr int FTile = 32;
 template <typename TG>
-__global__ __launch_bounds__(256) void k_cov_f64(const TG *g, int64_t ld, int B, int D, int nt,
+__global__ __launch_bounds__(256) void k_cov_f64(const TG *g, int64_t ld, int B, int D, int nt, int t0,
                                                  double *S_all) {
     const int blk = blockIdx.y;
     int ti, tj;
-    tile_coords(blockIdx.x, nt, ti, tj);
+    tile_coords(t0 + static_cast<int>(blockIdx.x), nt, ti, tj);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = lane & 15, q = lane >> 4;
     const int I = ti * FTile + 16 * (wave >> 1), J = tj * FTile + 16 * (wave & 1);
@@ -481,15 +481,20 @@ hipError_t launch_cov(const void *g, bool bf16, int64_t ld, int B, int D, int n_
 hipError_t launch_cov_f64(const void *g, bool f64_rows, int64_t ld, int B, int D, int n_blocks, double *S,
                           hipStream_t s) {
     if (B == 0 || n_blocks == 0) return hipSuccess;
-    const int nt = (D + FTile - 1) / FTile;
-    const dim3 grid(static_cast<unsigned>(nt * (nt + 1) / 2), static_cast<unsigned>(n_blocks));
-    if (f64_rows)
-        hipLaunchKernelGGL(k_cov_f64<double>, grid, dim3(256), 0, s, static_cast<const double *>(g), ld, B, D,
-                           nt, S);
-    else
-        hipLaunchKernelGGL(k_cov_f64<float>, grid, dim3(256), 0, s, static_cast<const float *>(g), ld, B, D,
-                           nt, S);
-    return hipGetLastError();
+    const int nt = (D + FTile - 1) / FTile, tiles = nt * (nt + 1) / 2;
+    const int most = static_cast<int>(kMaxGridThreads / 256 - 1);   // one launch up to D = 185,344
+    hipError_t e = hipSuccess;
+    for (int t0 = 0; t0 < tiles && e == hipSuccess; t0 += most) {
+        const dim3 grid(static_cast<unsigned>(min(most, tiles - t0)), static_cast<unsigned>(n_blocks));
+        if (f64_rows)
+            hipLaunchKernelGGL(k_cov_f64<double>, grid, dim3(256), 0, s, static_cast<const double *>(g), ld, B, D, nt, t0,
+                               S);
+        else
+            hipLaunchKernelGGL(k_cov_f64<float>, grid, dim3(256), 0, s, static_cast<const float *>(g), ld, B, D, nt, t0,
+                               S);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace logra
