@@ -522,8 +522,7 @@ int logra_self_influence_blocks(const float *S, int D, int n_blocks, int64_t N, 
     const bool bf16 = g_dtype == LOGRA_BF16;
     if (bf16 && (D % 8 || ld % 8)) return fail(LOGRA_ERR_INVALID_ARG, "bf16 gradients need D and ld multiples of 8");
     if (bf16 && ld >= (int64_t{1} << 22)) return fail(LOGRA_ERR_UNSUPPORTED, "bf16 gradients support ld < 4194304");
-    if ((!bf16 || D % 32) && rows > INT32_MAX)
-        return fail(LOGRA_ERR_UNSUPPORTED, "fp32 gradients, or D not a multiple of 32, support rows < 2^31");
+    if (!bf16 && rows > INT32_MAX) return fail(LOGRA_ERR_UNSUPPORTED, "fp32 gradients support rows < 2^31");
     if (damp_ratio >= 0.0) TRY(check_dev(S, "S", 4));
     if (self_out) TRY(check_dev(self_out, "self_out", 4));
     if (rsqrt_out) TRY(check_dev(rsqrt_out, "rsqrt_out", 4));

@@ -150,6 +150,9 @@ def test_self_influence_ws_and_validation(L):
     assert f(*args(D=60, ld=120)) == P.ERR_INVALID_ARG       # bf16 rows need multiples of 8
     assert f(*args(ld=1 << 22)) == P.ERR_UNSUPPORTED
     assert f(*args(rows=0, so=None)) == P.OK                # no rows: a no-op, no device access
+    assert f(*args(gdt=0, rows=1 << 31)) == P.ERR_UNSUPPORTED   # fp32: a workgroup per row
+    for D in (64, 40):                                      # bf16: any row count, whatever the width
+        assert f(*args(D=D, ld=2 * D, rows=1 << 31)) == P.ERR_INVALID_ARG and "S is NULL" in P.logra_last_error()
 
 
 def test_scaled_influence_validation(L):
