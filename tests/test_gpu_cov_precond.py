@@ -225,10 +225,14 @@ def test_precondition_not_pd():
     (65, 2, 33, "f32", "f64"), (129, 3, 5, "f32", "f64"), (255, 2, 64, "f64", "bf16"), (256, 300, 3, "bf16", "f64"),
     (256, 5, 1000, "f32", "f64"), (257, 2, 5, "f32", "f64"), (300, 1, 70, "bf16", "f32"), (512, 2, 129, "f64", "f64"),
     (777, 2, 9, "f32", "f64"), (1000, 24, 7, "f32", "f64"), (1024, 4, 64, "f32", "f64"),
-    (1288, 1, 200, "bf16", "f64")])
+    (1288, 1, 200, "bf16", "f64"),
+    # 32 right-hand sides a workgroup (256 workgroups or more), the second of them with a ragged rest
+    (64, 200, 45, "f32", "f64"), (40, 130, 33, "bf16", "f64"), (128, 130, 61, "f32", "f32"), (120, 130, 47, "f64", "f64"),
+    (200, 130, 50, "f32", "f64"), (264, 90, 70, "f32", "f64")])
 def test_precondition_panel_edges(D, nb, Q, idt, odt):
     """Widths around the 16-wide blocks, the 256-wide panels and their remainders, numbers of right-hand sides around
-    the 16, 32 and 64 of a workgroup, and both solve paths.  A float64 solve of a system of condition number kappa is
+    the 16 and 32 of a workgroup and the 64 of a block step's tile, both solve paths, and the solve's forms for widths
+    up to 64, 128 and 256 with 16 and with 32 right-hand sides a workgroup.  A float64 solve of a system of condition number kappa is
     within about D kappa 2^-53 of the oracle's; kappa <= 1 + 10 D here (damping 0.1 of the mean eigenvalue), so 1e-10
     leaves a factor of 50 at the widest; outputs in fewer bits add their rounding."""
     import torch

@@ -52,13 +52,14 @@ SELF_CASES = {
     "bf16_D320_two_passes": ("bf16", 320, 1, 257, 0, 1e-2),
     "bf16_D32_one_row": ("bf16", 32, 5, 1, 0, 0.1),
     "bf16_strided_rows": ("bf16", 64, 2, 130, 72, 0.1),
-    "bf16_D40_rowwise": ("bf16", 40, 2, 50, 0, 0.1),
+    "bf16_D40_one_narrow_chunk": ("bf16", 40, 2, 50, 0, 0.1),
     "bf16_D8_many_blocks": ("bf16", 8, 40, 700, 0, 0.1),
     "bf16_D72_narrow_chunk": ("bf16", 72, 3, 300, 0, 0.1),
     "bf16_D200_narrow_fourth_chunk": ("bf16", 200, 7, 600, 0, 0.1),
     "bf16_D256_ranges": ("bf16", 256, 9, 257, 2312, 0.1),
     "bf16_D264_narrow_second_pass": ("bf16", 264, 2, 300, 0, 0.1),
     "bf16_D584_three_passes": ("bf16", 584, 2, 100, 0, 0.1),
+    "bf16_D264_many_blocks": ("bf16", 264, 33, 20, 0, 0.1),   # the identity's columns 32 a workgroup
     "f32_D48_rowwise": ("f32", 48, 3, 33, 0, 0.1),
 }
 
