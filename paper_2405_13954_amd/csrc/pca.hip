@@ -533,8 +533,7 @@ __global__ __launch_bounds__(256) void k_act_cov_f32(const float *__restrict__ a
 // n4 = n rounded up to 4 and every element past n or p zero.  Four
 // consecutive rows of one column (the B operand of a 16x16x4 MFMA) are then
 // one 128-bit load, and a run of rows is one contiguous range.
-constexpr int kGramRows = 64;    // rows per partial sum of a Gram matrix
-constexpr int kGramChunk = 64;   // rows staged in LDS at a time
+constexpr int kGramRows = 64;    // rows per partial sum of a Gram matrix of more than 64 columns
 constexpr int kMaxP = 128;       // subspace width (at most 2 k for k <= 64)
 constexpr int kCqStages = 3;     // register pipeline depth of k_cq_regs
 constexpr int kJacobiSweeps = 40;   // at most this many Jacobi sweeps
@@ -809,77 +808,44 @@ __global__ __launch_bounds__(256) void k_cq_sum(const f32x4 *__restrict__ Zs, in
 }
 
 // Partial Gram sums G_c[a][b] = sum over rows r of chunk c of X[r][a] Y[r][b]
-// (fp64), a, b < p, for X, Y in row quads (n4 rows, zero past n), one
-// workgroup per chunk of kGramRows rows (64: 224 workgroups at n = 14336).
-// Rows are staged through LDS kGramChunk at a time (a longer chunk loads the
-// next rows into registers while the current ones are summed); an LDS read
-// of 128 bits gives one column's values in four consecutive rows.  PMAX (32,
-// 64 or 128) bounds p; a workgroup forms at most 4096 of the p x p sums (16
-// per thread), the blockIdx.y-th group of them.
-template <int PMAX>
+// (fp64), a, b < p, 64 < p <= 128, for X, Y in row quads (n4 rows, zero past n),
+// one workgroup per chunk of kGramRows rows (64: 224 chunks at n = 14,336).  The
+// chunk's rows are staged through LDS; an LDS read of 128 bits gives one
+// column's values in four consecutive rows.  A workgroup forms at most 4096 of
+// the p x p sums (16 per thread), the blockIdx.y-th group of them.
 __global__ __launch_bounds__(256) void k_gram_part(const float *__restrict__ X, const float *__restrict__ Y, int n,
                                                    int p, int pp, double *__restrict__ part) {
-    constexpr int kV = PMAX / 16;               // 128-bit loads per thread and operand, at most
-    constexpr int kU = PMAX * PMAX / 256 < 16 ? PMAX * PMAX / 256 : 16;   // outputs per thread, at most
-    __shared__ f32x4 xs[kGramChunk / 4 * PMAX], ys[kGramChunk / 4 * PMAX];
+    constexpr int kV = kGramRows / 4 * kMaxP / 256;   // 128-bit loads per thread and operand, at most
+    constexpr int kU = 16;                            // outputs per thread
+    __shared__ f32x4 xs[kGramRows / 4 * kMaxP], ys[kGramRows / 4 * kMaxP];
     const int tid = threadIdx.x;
-    const int n4 = round4(n);
-    const int r0 = blockIdx.x * kGramRows;
-    const int rend = min(n4, r0 + kGramRows);
+    const int r0 = blockIdx.x * kGramRows, nq = (min(round4(n), r0 + kGramRows) - r0) / 4;
     const int np = p * p;
-    const int nv = pp / 16;                     // 128-bit loads per thread of a full chunk
-    const f32x4 *X4 = reinterpret_cast<const f32x4 *>(X);
-    const f32x4 *Y4 = reinterpret_cast<const f32x4 *>(Y);
-    f32x4 xr[kV], yr[kV];
-    auto fetch = [&](int c0) {
-        const int lim = (min(kGramChunk, rend - c0) / 4) * pp;   // 128-bit elements of this chunk
-        const size_t base = static_cast<size_t>(c0 / 4) * pp;
+    const f32x4 *X4 = reinterpret_cast<const f32x4 *>(X) + static_cast<size_t>(r0 / 4) * pp;
+    const f32x4 *Y4 = reinterpret_cast<const f32x4 *>(Y) + static_cast<size_t>(r0 / 4) * pp;
 #pragma unroll
-        for (int v = 0; v < kV; ++v) {
-            const int f = tid + 256 * v;
-            const bool ok = v < nv && f < lim;
-            xr[v] = ok ? X4[base + f] : f32x4{0.f, 0.f, 0.f, 0.f};
-            yr[v] = ok ? Y4[base + f] : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int v = 0; v < kV; ++v) {
+        const int f = tid + 256 * v;
+        if (f < nq * pp) {
+            xs[f] = X4[f];
+            ys[f] = Y4[f];
         }
-    };
-    double acc[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) acc[u] = 0.0;
-    const int e0 = blockIdx.y * 256 * kU;       // first output of this workgroup
-    if (r0 < rend) fetch(r0);
-    for (int c0 = r0; c0 < rend; c0 += kGramChunk) {
-        const int nq = min(kGramChunk, rend - c0) / 4;
-#pragma unroll
-        for (int v = 0; v < kV; ++v) {
-            const int f = tid + 256 * v;
-            if (v < nv && f < nq * pp) {
-                xs[f] = xr[v];
-                ys[f] = yr[v];
-            }
-        }
-        __syncthreads();
-        if (c0 + kGramChunk < rend) fetch(c0 + kGramChunk);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int e = e0 + tid + 256 * u;
-            if (e < np) {
-                const int a = e / p, b = e - (e / p) * p;
-                double s = acc[u];
-                for (int qq = 0; qq < nq; ++qq) {
-                    const f32x4 xv = xs[qq * pp + a], yv = ys[qq * pp + b];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s = fma(static_cast<double>(xv[r]), static_cast<double>(yv[r]), s);
-                }
-                acc[u] = s;
-            }
-        }
-        __syncthreads();
     }
+    __syncthreads();
     double *dst = part + static_cast<size_t>(blockIdx.x) * np;
+    const int e0 = blockIdx.y * 256 * kU;       // first output of this workgroup
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
         const int e = e0 + tid + 256 * u;
-        if (e < np) dst[e] = acc[u];
+        if (e >= np) continue;
+        const int a = e / p, b = e - (e / p) * p;
+        double s = 0.0;
+        for (int qq = 0; qq < nq; ++qq) {
+            const f32x4 xv = xs[qq * pp + a], yv = ys[qq * pp + b];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s = fma(static_cast<double>(xv[r]), static_cast<double>(yv[r]), s);
+        }
+        dst[e] = s;
     }
 }
 
@@ -893,7 +859,8 @@ __host__ __device__ constexpr int gram_rows(int pp) { return pp <= 32 ? 256 : pp
 // row 4 q + t goes to the t-th MFMA of a step, for both operands), and the
 // waves' sums are folded through LDS in fixed order.  Y may still be in
 // `splits` partials (splits > 1, at Ys, a distance of n4 pp apart): they are
-// added in fp64, rounded once and also written to Y.  SAME: X is Y.
+// added in fp64 and rounded once.  SAME: X is Y, and the sum of its splits is
+// also written to Y for the kernel that follows.
 // Measured, n = 768 to 3,072, p = 32, 6 to 8 splits: 7.0-7.7 us with 256-row chunks; a thread per output
 // over 64-row chunks staged in LDS took 6.1 after a 4.2 us sum of the splits.
 template <int NB, bool SAME>
@@ -957,7 +924,7 @@ __global__ __launch_bounds__(512) void k_gram_mfma(const float *__restrict__ X, 
     for (int u = 0; u < kSteps; ++u) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            if (splits > 1 && in[u]) reinterpret_cast<f32x4 *>(Y)[at[u] + 16 * b] = y[u][b];
+            if (SAME && splits > 1 && in[u]) reinterpret_cast<f32x4 *>(Y)[at[u] + 16 * b] = y[u][b];
             y[u][b] = in[u] ? y[u][b] : f32x4{0.f, 0.f, 0.f, 0.f};
             if (SAME) x[u][b] = y[u][b];
         }
@@ -1002,7 +969,8 @@ __global__ __launch_bounds__(512) void k_gram_mfma(const float *__restrict__ X, 
 
 inline int gram_chunks(int n, int pp) { return (round4(n) + gram_rows(pp) - 1) / gram_rows(pp); }
 
-// Partial sums of X^T Y; Y is the sum of `splits` partials at Ys (and written) when there are several.
+// Partial sums of X^T Y; Y is the sum of `splits` partials at Ys when there are several (and left in Y if it
+// is X, or for more than 64 columns).
 void launch_gram(const float *X, const float *Ys, float *Y, int splits, int n, int p, int pp, double *part, hipStream_t s) {
     if (pp <= 64) {
         const dim3 grid(static_cast<unsigned>(gram_chunks(n, pp)));
@@ -1026,7 +994,7 @@ void launch_gram(const float *X, const float *Ys, float *Y, int splits, int n, i
                            reinterpret_cast<const f32x4 *>(Ys), nv, splits, reinterpret_cast<f32x4 *>(Y));
     }
     const dim3 grid(static_cast<unsigned>(gram_chunks(n, pp)), static_cast<unsigned>((p * p + 4095) / 4096));
-    hipLaunchKernelGGL(k_gram_part<128>, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
+    hipLaunchKernelGGL(k_gram_part, grid, dim3(256), 0, s, X, Y, n, p, pp, part);
 }
 
 // G = sum of the chunk partials, in chunk order, into A (all threads).  The
@@ -1135,10 +1103,10 @@ __device__ __forceinline__ void axpy_lds(double (&a)[RPT], const double *v, doub
     for (int i = 0; i < RPT; ++i) asm volatile("" : "+v"(a[i]));
 }
 
-// One workgroup; the matrix is padded to PM (32, 64 or 128) with the
-// identity, whose factor and inverse are the identity.  Thread (c, h) keeps
-// rows RPT h .. RPT h + RPT - 1 of column c in registers (RPT = min(PM, 64)):
-// for PM <= 64 one wave, lane c holding the whole column; for PM = 128 four
+// One workgroup; the matrix is padded to PM (64 or 128) with the identity, whose
+// factor and inverse are the identity.  Thread (c, h) keeps rows RPT h .. RPT h +
+// RPT - 1 of column c in registers (RPT = 64):
+// for PM = 64 one wave, lane c holding the whole column; for PM = 128 four
 // waves, c = 64 (wave & 1) + lane and h = wave >> 1.  The shifted Cholesky
 // G + eps (tr G / p) I = R^T R runs in outer-product form: step j passes row
 // j through LDS (zeros left of the diagonal) and every thread updates its
@@ -1156,8 +1124,8 @@ __device__ __forceinline__ void axpy_lds(double (&a)[RPT], const double *v, doub
 template <int PM>
 __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict__ part, int chunks, int p,
                                                        double *__restrict__ RinvT) {
-    constexpr int RPT = PM < 64 ? PM : 64;
-    constexpr int NW = PM <= 64 ? 1 : 4;   // waves that factorise
+    constexpr int RPT = 64;
+    constexpr int NW = PM == 64 ? 1 : 4;   // waves that factorise
     constexpr int RS = PM + 2;   // stride of the column-major copies of R and R^{-T} (even: 16-byte pairs)
     __shared__ __attribute__((aligned(16))) double A[PM * RS];   // G [p][p]; then R by columns; then R^{-T} by rows
     __shared__ __attribute__((aligned(16))) double buf[2][PM];
@@ -1166,7 +1134,6 @@ __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict_
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = NW == 4 ? 64 * (wave & 1) + lane : lane;
     const int h = NW == 4 ? wave >> 1 : 0;
-    const bool col = c < PM;   // lanes past PM (PM = 32) hold no column
     sum_partials(part, chunks, p * p, A, tid);
     __syncthreads();
     if (wave >= NW) return;
@@ -1189,14 +1156,14 @@ __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict_
         constexpr int j = decltype(step)::value;
         constexpr int hj = j / RPT, jj = j % RPT;
         double *row = buf[j & 1];
-        if (h == hj && col) row[c] = c >= j ? a[jj] : 0.0;   // zeros left of the diagonal: no update there
+        if (h == hj) row[c] = c >= j ? a[jj] : 0.0;   // zeros left of the diagonal: no update there
         sync();
         // one wave: the pivot from lane j's register and f from the lane's own
         // (the values the row holds), so the reciprocal need not wait for LDS
         const double d = NW == 1 ? readlane_d(a[jj], j) : row[j];
         const double e = d > 0.0 ? d : 1.0;
         if (tid == 0) rdiag[j] = e;
-        const double f = col && c > j ? (NW == 1 ? a[jj] : row[c]) / e : 0.0;
+        const double f = c > j ? (NW == 1 ? a[jj] : row[c]) / e : 0.0;
         const double keep = a[jj];   // row j itself is final
         axpy_lds<RPT>(a, row + RPT * h, f);
         a[jj] = h == hj ? keep : a[jj];
@@ -1208,7 +1175,7 @@ __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict_
     for (int i = 0; i < RPT; ++i) {
         const int r = RPT * h + i;
         const double rr = rdiag[r];
-        if (col) A[c * RS + r] = r < c ? a[i] / rr : r == c ? rr : 0.0;   // R_rc, column c contiguous
+        A[c * RS + r] = r < c ? a[i] / rr : r == c ? rr : 0.0;   // R_rc, column c contiguous
         a[i] = r == c ? 1.0 : 0.0;
     }
     sync();
@@ -1219,20 +1186,18 @@ __global__ __launch_bounds__(256) void k_chol_inv_cols(const double *__restrict_
         const double *Rj = A + j * RS;   // column j of R
         if (h == hj) {
             a[jj] = a[jj] / Rj[j];
-            if (NW > 1 && col) row[c] = a[jj];
+            if (NW > 1) row[c] = a[jj];
         }
         sync();
         // one wave: row j of X is the lane's own register
-        const double x = col ? (NW == 1 ? a[jj] : row[c]) : 0.0;
+        const double x = NW == 1 ? a[jj] : row[c];
         const double keep = a[jj];   // row j of X is final; R is zero below its diagonal
         axpy_lds<RPT>(a, Rj + RPT * h, x);
         a[jj] = h == hj ? keep : a[jj];
     });
     sync();   // every read of R is done
-    if (col) {
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) A[c * RS + RPT * h + i] = a[i];   // row c of R^{-T} is column c of R^{-1}
-    }
+    for (int i = 0; i < RPT; ++i) A[c * RS + RPT * h + i] = a[i];   // row c of R^{-T} is column c of R^{-1}
     sync();
     for (int e = tid; e < p * p; e += kWave * NW) {
         const int r = e / p;

@@ -51,8 +51,7 @@ struct WsLayout {
 
 inline int padded_q(int Q) { return (Q + 63) / 64 * 64; }
 
-inline WsLayout ws_layout(void *ws, int D, int n_blocks, int Q) {
-    (void)Q;
+inline WsLayout ws_layout(void *ws, int D, int n_blocks) {
     char *p = static_cast<char *>(ws);
     const size_t nb = static_cast<size_t>(n_blocks);
     WsLayout w;
@@ -1101,7 +1100,7 @@ bf16_bits *self_influence_w(void *ws, int D, int n_blocks, bool lo) {
 
 float *self_influence_part(void *ws, int D, int n_blocks, size_t *bytes) {
     *bytes = sizeof(double) * static_cast<size_t>(n_blocks) * D * padded_q(D);
-    return reinterpret_cast<float *>(ws_layout(ws, D, n_blocks, D).Y);
+    return reinterpret_cast<float *>(ws_layout(ws, D, n_blocks).Y);
 }
 
 size_t precond_ws_bytes(int D, int n_blocks, int Q) {
@@ -1110,7 +1109,7 @@ size_t precond_ws_bytes(int D, int n_blocks, int Q) {
            align256(sizeof(double) * nb * D * padded_q(Q));
 }
 
-int *precond_info_ptr(void *ws, int D, int n_blocks) { return ws_layout(ws, D, n_blocks, 0).info; }
+int *precond_info_ptr(void *ws, int D, int n_blocks) { return ws_layout(ws, D, n_blocks).info; }
 
 namespace {
 // Dispatch over the element types of an input and an output (dtype codes).
@@ -1144,7 +1143,7 @@ hipError_t launch_copy_rows(const void *src, int in_dt, int64_t ld_in, int rows,
 hipError_t launch_precondition(const void *S, bool s_f64, int D, int n_blocks, int64_t N, double damp_ratio,
                                const void *g_test, int in_dt, int64_t ld_in, int Q, void *g_out, int out_dt,
                                int64_t ld_out, void *ws, hipStream_t s) {
-    const WsLayout w = ws_layout(ws, D, n_blocks, Q);
+    const WsLayout w = ws_layout(ws, D, n_blocks);
     hipError_t e = launch_factor(S, s_f64, D, n_blocks, N, damp_ratio, w, s);
     if (e != hipSuccess || Q == 0) return e;
     const int Qp = padded_q(Q);
@@ -1164,7 +1163,7 @@ hipError_t launch_precondition(const void *S, bool s_f64, int D, int n_blocks, i
 
 hipError_t launch_inverse_factor(const float *S, int D, int n_blocks, int64_t N, double damp_ratio,
                                  bool interleaved, void *ws, hipStream_t s) {
-    const WsLayout w = ws_layout(ws, D, n_blocks, D);
+    const WsLayout w = ws_layout(ws, D, n_blocks);
     bf16_bits *hi = self_influence_w(ws, D, n_blocks, false), *lo = self_influence_w(ws, D, n_blocks, true);
     const bool ident = damp_ratio < 0;
     const double *src = w.A;   // D <= 256: W itself

@@ -355,8 +355,7 @@ __global__ __launch_bounds__(256) void k_self_influence_fold(const float *__rest
 // fp32 gradients: one workgroup per gradient; thread d forms output d of W_l g_l
 // with the hi + lo halves (all D columns), a fixed-order block sum adds the
 // squares, blocks in order.  For small problems.
-template <typename TIn>
-__global__ __launch_bounds__(256) void k_self_influence_rows(const TIn *__restrict__ g, int64_t ld, int D,
+__global__ __launch_bounds__(256) void k_self_influence_rows(const float *__restrict__ g, int64_t ld, int D,
                                                              int n_blocks, const bf16_bits *__restrict__ w_hi,
                                                              const bf16_bits *__restrict__ w_lo,
                                                              float *__restrict__ self_out,
@@ -367,14 +366,14 @@ __global__ __launch_bounds__(256) void k_self_influence_rows(const TIn *__restri
     const int Dp = (D + 255) / 256 * 256;
     float total = 0.f;
     for (int l = 0; l < n_blocks; ++l) {
-        const TIn *gl = g + j * ld + static_cast<int64_t>(l) * D;
+        const float *gl = g + j * ld + static_cast<int64_t>(l) * D;
         float part = 0.f;
         for (int d = tid; d < D; d += 256) {
             const bf16_bits *h = w_hi + (static_cast<size_t>(l) * Dp + d) * D;
             const bf16_bits *lo = w_lo + (static_cast<size_t>(l) * Dp + d) * D;
             float y = 0.f;
             for (int k = 0; k < D; ++k)
-                y = __builtin_fmaf(bf16_to_f32(h[k]) + bf16_to_f32(lo[k]), static_cast<float>(load_in_d<TIn>(gl + k)), y);
+                y = __builtin_fmaf(bf16_to_f32(h[k]) + bf16_to_f32(lo[k]), gl[k], y);
             part = __builtin_fmaf(y, y, part);
         }
         red[tid] = part;
@@ -423,7 +422,7 @@ hipError_t launch_self_influence(const void *g, bool bf16, int64_t ld, int64_t r
             hipLaunchKernelGGL(k_self_influence_fold, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0, s, part,
                                rows, ranges, self_out, rsqrt_out);
     } else {
-        hipLaunchKernelGGL(k_self_influence_rows<float>, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_self_influence_rows, dim3(static_cast<unsigned>(rows)), dim3(256), 0, s,
                            static_cast<const float *>(g), ld, D, n_blocks, hi, lo, self_out, rsqrt_out);
     }
     return hipGetLastError();
