@@ -139,11 +139,12 @@ __device__ __forceinline__ double readlane_d(double v, int src) {
 }
 
 // 1 / sqrt(x) to about an ulp: the hardware estimate (relative error below
-// 2^-20) and one third-order step, whose residual h is a NaN for x = inf (the
-// maximum drops it: 1 / sqrt(inf) is 0).
+// 2^-20) and one third-order step.  For x = inf the step's residual h is a NaN;
+// with MAYBE_INF a maximum drops it and the result is 0.
+template <bool MAYBE_INF = false>
 __device__ __forceinline__ double rsqrt_d(double x) {
     const double y = __builtin_amdgcn_rsq(x);
-    const double h = __builtin_fmax(fma(-x * y, y, 1.0), -1.0);
+    const double r = fma(-x * y, y, 1.0), h = MAYBE_INF ? __builtin_fmax(r, -1.0) : r;
     return fma(y * h, fma(h, 0.375, 0.5), y);
 }
 

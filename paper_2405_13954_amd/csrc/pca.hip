@@ -1029,8 +1029,8 @@ __device__ __forceinline__ void sum_partials(const double *__restrict__ part, in
 }
 
 // G = the sum of the chunk partials, written over chunk 0's slot.  The Gram
-// partials come in 64-row chunks (224 at n = 14336: 1.8 MB at p = 32, 29 MB
-// at p = 128), too many for one workgroup to gather; spread over the chip
+// partials come in chunks of gram_rows rows (at n = 14,336: 56 of 256 rows for p <=
+// 32, 112 of 128 for p <= 64, else 224 of 64, 29 MB at p = 128), too many for one workgroup to gather; spread over the chip
 // they take a few microseconds, and the one-workgroup kernels then read a
 // single chunk.  A workgroup takes 64 elements; wave w sums the w-th quarter
 // of the chunks of each, in chunk order, and the quarters are added in a
@@ -1274,6 +1274,12 @@ __global__ __launch_bounds__(256) void k_apply_rinv(const float *__restrict__ Z,
 // Measured, n = 768 to 3,072, p = 32: 12 us; a launch for the Cholesky in column
 // form with back substitution took 21.2, the sum of 48 partials before it 3.3
 // and a lane per row quad with fp64 FMAs after it 7.2.
+// kCholChunks: every slot costs each iteration, used or not (absent partials read
+// the last one: n = 768, p = 32, 3 partials: 21.1 us an iteration with 6 slots, 22.0
+// with 12, 23.7 with 24), and an n with more partials pays k_sum_parts and its
+// launch (n = 3,072, 12 partials: 31.0 us with 6 slots, 29.6 with 12, 30.1 with 16;
+// n = 4,096, 16 partials: 35.6 with 12 and 33.7 with 16; n = 6,144, 24: 54.7 with 12
+// and 53.3 with 24). 12 serves the widest layers of a small model.
 constexpr int kCholChunks = 12;
 __device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }   // v has its value here
 template <int NB>
@@ -1712,8 +1718,8 @@ inline size_t rot_bytes(int p) {
 }
 
 // Z = C Q: row blocks of 16 MR rows per workgroup, and the columns of C cut
-// into splits of kr (a multiple of 64, at least 512 unless n is smaller) so
-// that the grid has about 2048 workgroups.
+// into splits of kr (a multiple of 64) so that the grid has up to about 2,048
+// workgroups.
 inline int cq_mr(int pp) { return pp / 16 <= 4 ? 4 : 2; }
 inline int cq_kr(int n, int pp) {
     const int rb = (n + 16 * cq_mr(pp) - 1) / (16 * cq_mr(pp));

@@ -201,7 +201,7 @@ __device__ __forceinline__ void factor_block(const TS *S_all, int64_t N, double 
             // then the others beside the next reciprocal root (the order is fixed:
             // left alone, each column's updates move into the chain of its pivot).
             double piv = readlane_d(x[0], 0), mine = piv;   // lane j keeps pivot j
-            double inv = rsqrt_d(piv);
+            double inv = rsqrt_d<true>(piv);
 #pragma unroll
             for (int j = 0; j < FB; ++j) {
                 x[j] *= inv;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void factor_block(const TS *S_all, int64_t N, double 
                     piv = readlane_d(x[j + 1], j + 1);
                     mine = lane == j + 1 ? piv : mine;
                     __builtin_amdgcn_sched_barrier(0);
-                    inv = rsqrt_d(piv);
+                    inv = rsqrt_d<true>(piv);
 #pragma unroll
                     for (int k = j + 2; k < FB; ++k) x[k] = fma(-x[j], readlane_d(x[j], k), x[k]);
                 }

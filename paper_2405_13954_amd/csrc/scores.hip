@@ -307,11 +307,12 @@ __global__ __launch_bounds__(GT, 1) void k_scores_dma(const bf16_bits *__restric
 // multiplies 16x16x32 MFMA fragments read from the ring: no barrier before the
 // final fold, which adds the four partial tiles in fixed order through LDS.
 // The workgroups of one train slab go to one XCD, as in k_scores_dma.
-// Bound by HBM where few queries meet many rows, otherwise by the copies into
-// one CU's LDS (about 80 GB/s a CU; loads of the same fragments into registers
-// reached 50).  Measured, D = 57,344, against the 256 x 256 tiles: 256 x 256
-// rows 954 -> 68 us, 4 queries x 4,096 rows 887 -> 87, 4 x 65,536 1256 -> 1099
-// (6.8 TB/s), 32 x 65,536 1261 -> 1185, 256 x 4,096 956 -> 290.
+// Bound by HBM where few queries meet many rows.  Otherwise every workgroup's
+// copies arrive at 50 to 56 GB/s (256 x 256 rows: 3.67 MB in 66 us), far from the
+// HBM and MFMA rates of the chip; what holds them there has not been found.
+// Measured, D = 57,344, against the 256 x 256 tiles: 256 x 256 rows 954 -> 68 us,
+// 4 queries x 4,096 rows 887 -> 87, 4 x 65,536 1256 -> 1099 (6.8 TB/s), 32 x
+// 65,536 1261 -> 1185, 256 x 4,096 956 -> 290.
 //
 // LDS slab: rows of 128 bytes, chunk c of row r at position c ^ ((r >> 1) & 7),
 // so that the 16 rows read by a quarter-wave hit 16 different 16-byte banks.
