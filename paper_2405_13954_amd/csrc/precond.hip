@@ -156,7 +156,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // Bound by fp64 MFMA issue on one CU (11 MFLOP) and by the chain of the 16
 // pivots of a diagonal block (a SIMD that issues fp64 MFMAs lets one vector
 // instruction of another wave through per MFMA, so the eighth wave's partner
-// has to run dry first).  Measured: 224 blocks of 256 125 us, one 111; with the
+// has to run dry first).  Measured: 224 blocks of 256 119 to 125 us, one 111; with the
 // factor, panel, update and tile-inverse kernels of 64-wide steps before it:
 // 790 us.  All 128 products of panel and pivots in every wave, publication of
 // each column through LDS and both triangles of W stored: 185.
@@ -363,8 +363,8 @@ __global__ __launch_bounds__(kFactorThreads, 2) void k_factor(const TS *S_all, i
 // 8: row v; 4: row v % 4 and half of the columns).  A wave streams its rows (or
 // columns) of W from memory, mostly the L2, four units ahead, and reads the
 // right-hand sides as LDS fragments.  Measured, 224 blocks of 256, 1,024
-// right-hand sides (31 GFLOP): 746 us in workgroups of 32, 885 in workgroups of
-// 64, whose loads and stores no second workgroup of the CU covers; blocked
+// right-hand sides (30 GFLOP): 650 to 740 us by run (675 in the benchmark's trace) in
+// workgroups of 32, 885 in workgroups of 64, whose loads and stores no second workgroup of the CU covers; blocked
 // substitution in 64-wide steps took 1,200.
 enum SolveSrc { kFromG = 0, kFromY = 1, kFromIdent = 2 };
 struct SolveArgs {

@@ -474,7 +474,8 @@ __global__ __launch_bounds__(GT, 1) void k_scores_small(const bf16_bits *__restr
 // row r, for the four MFMAs of the unit, of both operands), and the four
 // partial tiles are added in fixed order through LDS.  Scales (normalised
 // scores) multiply in float64 before the rounding.  Bound by latency at the sizes
-// of fp32 workloads: 8 x 32 rows of 1,024 columns 22 us; 116 in k_scores_f64_chain.
+// of fp32 workloads: a call of 8 x 32 rows of 1,024 columns 22 us (the kernel 14); 116
+// in k_scores_f64_chain.
 template <int F, typename TA, typename TB>
 __global__ __launch_bounds__(256) void k_scores_f64acc(const TA *te, int64_t ld_te, int Q, const TB *tr,
                                                        int64_t ld_tr, int64_t N, int D, float *s, int64_t ld_s,

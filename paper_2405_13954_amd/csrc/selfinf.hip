@@ -131,8 +131,8 @@ __device__ __forceinline__ void finish_rows(const float (&psum)[4], float *rowsu
 // blockIdx.y: one of gridDim.y ranges of blocks, whose sums go to
 // part[range][gradient] when there are several (k_self_influence_fold adds
 // them).  32,768 gradients are 128 workgroups, half the chip, without ranges.
-// Measured, 32,768 gradients of 224 blocks of 256: about 1.25 ms; 2,645 us with
-// all products and one range.
+// Measured, 32,768 gradients of 224 blocks of 256: 1.25 to 1.43 ms by run; 2,645 us
+// with all products and one range.
 constexpr int DBK = 64;                          // columns per step
 constexpr int kDSlab = 256 * DBK * 2;            // bytes of one operand slab
 constexpr int kDStA = 2, kDStB = 3;
